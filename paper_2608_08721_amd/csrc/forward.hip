@@ -91,7 +91,7 @@ struct VerifyWs {
 
 struct VerifyPlan {
   int MT, batch;
-  bool wide;  // bf16 blocks of 64 < rows <= kWideRows: all rows per workgroup, activations via LDS
+  bool wide;  // bf16 bounds of more than 64 rows: the batched GEMMs
   WidePlan w[5];
   size_t part_floats;
   AttnPlan attn;
@@ -101,16 +101,19 @@ static VerifyPlan plan_verify(const Shape& s, const ModelLayout& ml, int batch, 
   VerifyPlan v;
   v.batch = batch;
   v.MT = max_rows > 64 ? 4 : (max_rows + 15) / 16;  // activation tiles per 64-row chunk
-  v.wide = s.dtype == LSV_DTYPE_BF16 && max_rows > 64 && max_rows <= kWideRows;
+  v.wide = s.dtype == LSV_DTYPE_BF16 && max_rows > 64;
   v.part_floats = 0;
   if (s.dtype == LSV_DTYPE_BF16 && residual_split_pairs(GEMM_O, ml.o.Nt))  // O and down: Nt = d / 16
     v.part_floats = split_pair_floats(ml.o.Nt, max_rows);
   if (v.wide) {
     const PackedMat* mats[5] = {&ml.qkv, &ml.o, &ml.gateup, &ml.down, &ml.lm_head};
     for (int k = 0; k < 5; ++k) {
-      v.w[k] = plan_wide(mats[k]->Nt, mats[k]->Kt);
-      const size_t pf = wide_part_floats(v.w[k], max_rows);
-      v.part_floats = pf > v.part_floats ? pf : v.part_floats;
+      v.w[k] = plan_wide(mats[k]->Nt, mats[k]->Kt, max_rows);
+      // a workspace serves every smaller row bound too, also one of a single chunk (more k ranges)
+      const int one = max_rows < kWideOneChunk ? max_rows : kWideOneChunk;
+      for (const size_t pf : {wide_part_floats(v.w[k], max_rows),
+                              wide_part_floats(plan_wide(mats[k]->Nt, mats[k]->Kt, one), one)})
+        v.part_floats = pf > v.part_floats ? pf : v.part_floats;
     }
   }
   v.attn = plan_attention(batch, s.nkv, max_ctx);

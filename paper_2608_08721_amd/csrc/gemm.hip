@@ -614,127 +614,163 @@ static int launch_typed(GemmKind kind, int MT, const GemmArgs& a, hipStream_t st
 }
 
 // ------------------------------------------------------------------ wide blocks
-// Batched verification (64 < rows <= kWideRows): the matrix cores become the bound.
-// Workgroup = 4 waves x 8 fragment rows (128 output columns) x one of `splits` k ranges;
-// the waves share the 8 weight fragments of each k-step through LDS and split the rows:
-// wave w keeps activation tiles w*MTW .. w*MTW+MTW-1 (MTW <= 5) in registers.  With more
+// Batched verification and prefill (more than 64 rows): the matrix cores become the bound.
+// Workgroup = 4 waves on one tile of kWideFR fragment rows (128 output columns) x one chunk of
+// the block's rows x one of `splits` k ranges.  With more
 // than one k range per tile, each workgroup writes fp32 partials and
 // gemm_wide_reduce_kernel adds them in split order (deterministic) and runs the epilogue,
 // one workgroup per (tile, 16 rows); the QKV reduce applies the rotary embedding and the Q
 // store / cache append.  An unsplit QKV runs the plain epilogue into an fp32 buffer
 // and qkv_rope_kernel does the rest.  The residual products (O, down) launch no reduce: the
 // row normalisation that follows each of them adds their partials to the residual stream.
-constexpr int kWideRingW = 10;  // k-steps of weight pieces in flight (register ring)
-constexpr int kWideRingX = 2;   // k-steps of activation fragments in flight (from L2)
+constexpr int kTileWaves = 4;
+constexpr int kTileLds = 10240;  // 16-byte pieces of LDS (all 160 KiB) for the stages of a workgroup
 
-// The body for MTW activation tiles per wave.  The workgroup's 8 weight fragments of a
-// k-step go HBM -> registers -> LDS (double buffered) and every wave reads all 8; each wave
-// keeps its own MTW activation tiles (rows wave*16*MTW ..) in registers, straight from L2.
-// A k-step is 8 LDS reads and 8 x MTW MFMAs per wave, each read feeding MTW of them.  Tiles
-// past the device row count are computed on clamped rows and never stored.
-// Ws: two buffers of 8 fragments.  The QKV projection never runs its fused epilogue here
-// (split K: the reduce does; one split: the projection, then qkv_rope_kernel).
+// The body for MTW activation tiles per wave (wave w: tiles w * MTW .. of the chunk; all eight
+// fragment rows).  A k-step's weight and activation fragments (1 KiB each, already in MFMA operand
+// order) go HBM / L2 -> LDS by direct loads, S k-steps ahead, and from LDS to registers one step
+// ahead of the products.  One barrier per k-step: behind it every wave's part of step c + 1
+// has landed and every wave holds step c in registers, so that slot is refilled at once with step
+// c + S.  The waits count loads: P per wave and k-step, retired in order.
+// Tile rows past the chunk's row tiles repeat its last one and are never stored.
 template <int EPI, int MTW>
-LSV_DEV void gemm_wide_body(const GemmArgs& a, const int M, u32x4_t* Ws) {
+LSV_DEV void gemm_tile_body(const GemmArgs& a, const int M, const int tile, const int j, const int mt_base,
+                            const int mt_end, u32x4_t* lds) {
   static_assert(EPI != EPI_QKV, "the batched QKV epilogue runs in the reduce or the RoPE kernel");
   using T = bf16_t;
-  constexpr int FR = kWideFR;
-  constexpr int RX = kWideRingX, RW = kWideRingW;
-  constexpr int PPT = FR * kWave / 256;  // 16-byte weight pieces per thread and k-step
-  static_assert(PPT * 256 == FR * kWave, "weight pieces divide over the threads");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
-  const int S = a.splits, tile = blockIdx.x / S, j = blockIdx.x % S;
-  const int k0 = (int)((long long)j * a.Kt / S), k1 = (int)((long long)(j + 1) * a.Kt / S), nk = k1 - k0;
-  const int tn0 = tile * FR, mt0 = wave * MTW;
-  const int tiles_alloc = (a.M_max + 15) / 16;  // activation tiles in the buffer
-  bool tvalid[FR];
+  constexpr int FRW = kWideFR, PW = FRW / kTileWaves, P = PW + MTW;
+  constexpr int ST = (FRW + kTileWaves * MTW) * kWave, S = kTileLds / ST;  // pieces per stage, stages
+  static_assert(FRW % kTileWaves == 0 && S >= 3 && P * S < 64, "whole loads per wave, counted by vmcnt");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int k0 = (int)((long long)j * a.Kt / a.splits), k1 = (int)((long long)(j + 1) * a.Kt / a.splits), nk = k1 - k0;
+  const int tn0 = tile * FRW;
+  const __amdgpu_buffer_rsrc_t wrs = stream_rsrc(a.W, (size_t)a.Nt * a.Kt * 1024);
+  const __amdgpu_buffer_rsrc_t xrs = stream_rsrc(a.x, (size_t)((a.M_max + 15) / 16) * a.Kt * 1024);
+  // this wave's loads of a k-step -- weight rows wave + 4 i and its own activation tiles -- each at
+  // a lane offset that is constant over the steps (the last block of frag_index may be shorter) plus
+  // a scalar one for the step, so that a step costs few scalar instructions
+  const int k_full = a.Kt / kFragBlock * kFragBlock;
+  uint32_t wv[2][PW], xv[MTW];
 #pragma unroll
-  for (int f = 0; f < FR; ++f) tvalid[f] = tn0 + f < a.Nt;
-  const GLOBAL u32x4_t* wg = (const GLOBAL u32x4_t*)a.W;
-  const GLOBAL u32x4_t* xg = (const GLOBAL u32x4_t*)a.x + lane;
-  int xt[MTW];  // activation tile of each of the wave's slots (clamped into the buffer)
-#pragma unroll
-  for (int mt = 0; mt < MTW; ++mt) xt[mt] = min(mt0 + mt, tiles_alloc - 1);
-
-  // Register rings: weight pieces of the next RW k-steps (piece p = (fragment p / 64, lane
-  // p % 64)), and this wave's activation fragments of the next RX.
-  u32x4_t wst[RW][PPT], xr[RX][MTW];
-  auto issue_w = [&](int sw, int k) {
-    const int kk = max(min(k, nk - 1), 0);
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) {
-      const int p = tid + 256 * i, f = p / kWave, ln = p % kWave;
-      const int fr = tn0 + f < a.Nt ? tn0 + f : 0;
-      wst[sw][i] = load_stream(&wg[frag_index(fr, k0 + kk, a.Nt, a.Kt) * kWave + ln]);
-    }
-  };
-  auto issue_x = [&](int sx, int k) {
-    const int kk = max(min(k, nk - 1), 0);
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) xr[sx][mt] = xg[((size_t)xt[mt] * a.Kt + k0 + kk) * kWave];
-  };
-  auto store = [&](int sw, int buf) {
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) Ws[buf * FR * kWave + tid + 256 * i] = wst[sw][i];
-  };
-  f32x4_t acc[FR][MTW];
-#pragma unroll
-  for (int f = 0; f < FR; ++f)
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) acc[f][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  u32x4_t xcur[MTW];
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int f = 0; f < FR; ++f) {
-      const u32x4_t w = Ws[(buf * FR + f) * kWave + lane];
-#pragma unroll
-      for (int mt = 0; mt < MTW; ++mt) mfma_frag(w, xcur[mt], acc[f][mt], T{});
-    }
-  };
-  // k-step c: its weights sit in LDS buffer c & 1 (stored during step c - 1); the weights of
-  // step c + 1 move from their register stage to the other buffer and that stage takes step
-  // c + 1 + RW; the activation stage of step c takes step c + RX.  One barrier per step.
-  // u = c mod UNR (a compile-time constant where step is called), so ring stages are static.
-  constexpr int UNR = RX % RW == 0 ? RX : (RW % RX == 0 ? RW : RX * RW);
-  auto step = [&](int c, int u) {
-    const int sx = u % RX, sw = (u + 1) % RW;
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) xcur[mt] = xr[sx][mt];
-    if (c + 1 < nk) store(sw, (c + 1) & 1);
-    issue_w(sw, c + 1 + RW);
-    issue_x(sx, c + RX);
-    compute(c & 1);
-    __syncthreads();
-  };
-#pragma unroll
-  for (int sx = 0; sx < RX; ++sx) issue_x(sx, sx);
-#pragma unroll
-  for (int sw = 0; sw < RW; ++sw) issue_w(sw, sw);
-  store(0, 0);
-  issue_w(0, RW);
-  __syncthreads();
-  int c = 0;
-  for (; c + UNR <= nk; c += UNR) {
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) step(c + u, u);
+  for (int i = 0; i < PW; ++i) {
+    const int row = min(tn0 + wave + kTileWaves * i, a.Nt - 1);
+    wv[0][i] = (uint32_t)(row * kFragBlock) * 1024u + lane * 16;
+    wv[1][i] = (uint32_t)(row * (a.Kt - k_full)) * 1024u + lane * 16;
   }
 #pragma unroll
-  for (int u = 0; u < UNR; ++u)
-    if (c + u < nk) step(c + u, u);
+  for (int t = 0; t < MTW; ++t) xv[t] = (uint32_t)(min(mt_base + wave * MTW + t, mt_end - 1) * a.Kt) * 1024u + lane * 16;
+  struct Refill {  // the scalars of one step's loads
+    int base;         // its stage in the LDS
+    uint32_t wk, xk;  // byte offsets of the k-step in the weights and the activations
+    bool tail;        // in the last, shorter block of frag_index
+  };
+  auto refill_of = [&](int slot, int c) {
+    const int k = k0 + min(c, nk - 1);  // steps past the range re-load the last one
+    return Refill{slot * ST, (uint32_t)((k & -kFragBlock) * a.Nt + (k & (kFragBlock - 1))) * 1024u, (uint32_t)k * 1024u,
+                  k >= k_full};
+  };
+  auto issue = [&](const Refill& r) {
+#pragma unroll
+    for (int i = 0; i < PW; ++i)
+      load_lds<kBufferStream>(wrs, lds + r.base + (wave + kTileWaves * i) * kWave, r.tail ? wv[1][i] : wv[0][i], r.wk);
+#pragma unroll
+    for (int t = 0; t < MTW; ++t)
+      load_lds<0>(xrs, lds + r.base + (FRW + wave * MTW + t) * kWave, xv[t], r.xk);
+  };
+  f32x4_t acc[FRW][MTW];
+#pragma unroll
+  for (int f = 0; f < FRW; ++f)
+#pragma unroll
+    for (int t = 0; t < MTW; ++t) acc[f][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  u32x4_t wf[2][FRW], xf[2][MTW];
+  auto read = [&](int r, const u32x4_t* pw, const u32x4_t* px) {
+#pragma unroll
+    for (int f = 0; f < FRW; ++f) wf[r][f] = pw[f * kWave];
+#pragma unroll
+    for (int t = 0; t < MTW; ++t) xf[r][t] = px[t * kWave];
+  };
+  const int x_piece = (FRW + wave * MTW) * kWave + lane;
+  int slot = 0;
+  const u32x4_t *next_w = nullptr, *next_x = nullptr;  // this lane's pieces of step c + 1
+  Refill rf;
+  auto prepare = [&](int c) {
+    rf = refill_of(slot, c + S);
+    slot = slot + 1 == S ? 0 : slot + 1;
+    next_w = lds + slot * ST + lane;
+    next_x = lds + slot * ST + x_piece;
+  };
+  auto step = [&](int c, int u) {  // u = c mod 2: the register set that holds step c
+    wait_loads<P*(S - 2)>();  // this wave's part of step c + 1 has landed, and its reads of step c
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    read(u ^ 1, next_w, next_x);
+    issue(rf);
+    prepare(c + 1);
+#pragma unroll
+    for (int f = 0; f < FRW; ++f)
+#pragma unroll
+      for (int t = 0; t < MTW; ++t) mfma_frag(wf[u][f], xf[u][t], acc[f][t], T{});
+    // one wave per SIMD: what is issued between two products costs nothing, so the next step's LDS
+    // reads, the refill and the scalars of the step after go out one by one between them
+#pragma unroll
+    for (int i = 0; i < FRW + MTW; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);  // one load to LDS
+    }
+#pragma unroll
+    for (int i = 0; i < 10; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x006, 2, 0);  // two scalar or vector ALU instructions
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int s = 0; s < S; ++s) issue(refill_of(s, s));
+  prepare(0);
+  wait_loads<P*(S - 1)>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  read(0, lds + lane, lds + x_piece);
+  int c = 0;
+  if (nk & 1) {  // an odd step first, so that the loop leaves from one place
+    step(c++, 0);
+#pragma unroll
+    for (int f = 0; f < FRW; ++f) wf[0][f] = wf[1][f];
+#pragma unroll
+    for (int t = 0; t < MTW; ++t) xf[0][t] = xf[1][t];
+  }
+  for (; c < nk; c += 2) {
+    step(c, 0);
+    step(c + 1, 1);
+  }
+  wait_loads<0>();  // the re-loaded steps past the range land before the workgroup's LDS is given back
 
-  if (S > 1) {  // partial sums of this k range: [tile][split][M_max][kWideCols]
+  const int m0 = (mt_base + wave * MTW) * 16, M_end = min(M, mt_end * 16);
+  bool tvalid[FRW];
 #pragma unroll
-    for (int f = 0; f < FR; ++f)
+  for (int f = 0; f < FRW; ++f) tvalid[f] = tn0 + f < a.Nt;
+  if (a.splits > 1) {  // partial sums of this k range: [tile][split][M_max][kWideCols]
 #pragma unroll
-      for (int mt = 0; mt < MTW; ++mt) {
-        const int m = (mt0 + mt) * 16 + l16, col = f * 16 + 4 * g4;
-        if (m < M)
-          *(GLOBAL f32x4_t*)(a.part + (((size_t)tile * S + j) * a.M_max + m) * kWideCols + col) = acc[f][mt];
+    for (int f = 0; f < FRW; ++f)
+#pragma unroll
+      for (int t = 0; t < MTW; ++t) {
+        const int m = m0 + t * 16 + l16;
+        if (m < M_end && tvalid[f])
+          *(GLOBAL f32x4_t*)(a.part + (((size_t)tile * a.splits + j) * a.M_max + m) * kWideCols + f * 16 + 4 * g4) =
+              acc[f][t];
       }
     return;
   }
-  const f32x4_t none[FR][MTW] = {};
-  gemm_epilogue<T, MTW, FR, EPI, false>(a, M, mt0 * 16, tn0, tvalid, acc, none);
+  const f32x4_t none[FRW][MTW] = {};
+  gemm_epilogue<T, MTW, FRW, EPI, false>(a, M_end, m0, tn0, tvalid, acc, none);
 }
 
 // One launch for blocks under a batched row bound (64 < bound <= kWideRows).  Up to 64 device
@@ -742,11 +778,11 @@ LSV_DEV void gemm_wide_body(const GemmArgs& a, const int M, u32x4_t* Ws) {
 // tile (wave x grid + workgroup), so that the busy waves spread over the compute units -- and
 // streams its weights once, as gemm_kernel does (gate/up of the wider models with up to 32 rows
 // takes its eight-fragment-row configuration); more rows run the batched body on the
-// workgroup's (tile, k-split).  One launch instead of one of each kind, one of which would
-// find no work.
+// workgroup's (tile, k range, row chunk).  One launch instead of one of each kind, one of
+// which would find no work.
 template <int KIND, int WIDE_EPI>
-__global__ void __launch_bounds__(256) gemm_fused_kernel(GemmArgs a) {
-  __shared__ u32x4_t Ws[2 * kWideFR * kWave];
+__global__ void __launch_bounds__(64 * kTileWaves) gemm_fused_kernel(GemmArgs a) {
+  __shared__ u32x4_t lds[kTileLds];
   const int M = min(GL(a.row_offsets)[a.batch], a.M_max);  // never trust device rows beyond the host bound
   if (M <= 64) {
     if (M <= 0) return;
@@ -808,18 +844,24 @@ __global__ void __launch_bounds__(256) gemm_fused_kernel(GemmArgs a) {
       gemm_body<bf16_t, 4, S::TPW, 1, S::U, S::NS, S::EPI, 4>(a, M, vt, 0, nullptr, 0);
     return;
   }
-  if ((int)blockIdx.x >= (a.Nt + kWideFR - 1) / kWideFR * a.splits) return;
-  const int mtw = ((M + 15) / 16 + 3) / 4;  // activation tiles per wave
-  if (mtw <= 1)
-    gemm_wide_body<WIDE_EPI, 1>(a, M, Ws);
-  else if (mtw == 2)
-    gemm_wide_body<WIDE_EPI, 2>(a, M, Ws);
-  else if (mtw == 3)
-    gemm_wide_body<WIDE_EPI, 3>(a, M, Ws);
-  else if (mtw == 4)
-    gemm_wide_body<WIDE_EPI, 4>(a, M, Ws);
-  else
-    gemm_wide_body<WIDE_EPI, 5>(a, M, Ws);
+  // the row chunks of one (tile, k range) run side by side on one XCD (workgroup ids congruent mod
+  // 8), where the later readers of its weights find them in the L2
+  const int round = blockIdx.x >> 3, pair = (round / a.chunks) * 8 + (blockIdx.x & 7);
+  if (pair >= (a.Nt + kWideFR - 1) / kWideFR * a.splits) return;
+  const int mt_all = (M + 15) / 16, per = (mt_all + a.chunks - 1) / a.chunks;  // activation tiles per chunk
+  const int mt0 = round % a.chunks * per, mt1 = min(mt0 + per, mt_all);
+  if (mt0 >= mt1) return;
+  const int tile = pair / a.splits, j = pair % a.splits;
+  switch ((per + kTileWaves - 1) / kTileWaves) {  // activation tiles per wave
+    case 1: return gemm_tile_body<WIDE_EPI, 1>(a, M, tile, j, mt0, mt1, lds);
+    case 2: return gemm_tile_body<WIDE_EPI, 2>(a, M, tile, j, mt0, mt1, lds);
+    case 3: return gemm_tile_body<WIDE_EPI, 3>(a, M, tile, j, mt0, mt1, lds);
+    case 4: return gemm_tile_body<WIDE_EPI, 4>(a, M, tile, j, mt0, mt1, lds);
+    case 5: return gemm_tile_body<WIDE_EPI, 5>(a, M, tile, j, mt0, mt1, lds);
+    case 6: return gemm_tile_body<WIDE_EPI, 6>(a, M, tile, j, mt0, mt1, lds);
+    case 7: return gemm_tile_body<WIDE_EPI, 7>(a, M, tile, j, mt0, mt1, lds);
+    default: return gemm_tile_body<WIDE_EPI, 8>(a, M, tile, j, mt0, mt1, lds);  // LSV_MAX_ROWS in one chunk
+  }
 }
 
 // Split-K sums of the batched GEMM: one workgroup per (tile, 16 rows) adds the k ranges in
@@ -884,12 +926,16 @@ __global__ void __launch_bounds__(256) qkv_rope_kernel(GemmArgs a, const float* 
   }
 }
 
-WidePlan plan_wide(int Nt, int Kt) {
+WidePlan plan_wide(int Nt, int Kt, int max_rows) {
   WidePlan p;
   p.tiles = (Nt + kWideFR - 1) / kWideFR;
-  // one resident workgroup per compute unit (the accumulators fill the AGPRs); at least
-  // eight k-steps per workgroup
-  p.splits = 256 / p.tiles;
+  // one resident workgroup per compute unit (its stages fill the LDS); at least eight k-steps per
+  // workgroup.  Every row in one workgroup reads the weights once, but a product of few tiles would
+  // then take more k ranges, whose partials grow with rows x ranges: two row chunks halve them.
+  // Llama-3-8B width, 512 rows: gate/up (224 tiles) stays in one chunk; QKV (48), O and down (32)
+  // take two.
+  p.chunks = max_rows > kWideOneChunk && p.tiles <= kComputeUnits / 4 ? 2 : 1;
+  p.splits = kComputeUnits / (p.tiles * p.chunks);
   const int most = Kt / 8;
   if (p.splits > most) p.splits = most;
   if (p.splits < 1) p.splits = 1;
@@ -906,13 +952,15 @@ template <int KIND, int WIDE_EPI>
 static void launch_fused_one(const GemmArgs& a, const WidePlan& p, hipStream_t st) {
   using S = GemmShape<KIND, 4>;
   const int skinny_wgs = ((a.Nt + S::TPW - 1) / S::TPW + 3) / 4;
-  const int grid = p.tiles * p.splits > skinny_wgs ? p.tiles * p.splits : skinny_wgs;
-  hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI>), dim3((unsigned)grid), dim3(256), 0, st, a);
+  const int wide_wgs = p.chunks == 1 ? p.tiles * p.splits : (p.tiles * p.splits + 7) / 8 * 8 * p.chunks;
+  const int grid = wide_wgs > skinny_wgs ? wide_wgs : skinny_wgs;
+  hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI>), dim3((unsigned)grid), dim3(64 * kTileWaves), 0, st, a);
 }
 
 int launch_gemm_fused(GemmKind kind, const GemmArgs& a0, const WidePlan& p, hipStream_t st) {
   GemmArgs a = a0;
   a.splits = p.splits;
+  a.chunks = p.chunks;
   GemmArgs big = a;  // the passes after the batched body: only for more than 64 rows
   big.rows_lo = 64;
   const dim3 rgrid((unsigned)p.tiles, (unsigned)((a.M_max + 15) / 16));

@@ -46,6 +46,18 @@ LSV_DEV u32x4_t load_stream(__amdgpu_buffer_rsrc_t r, uint32_t off) {
 // The same through a global address (the batched GEMM body, where buffer loads lost 0.3%).
 template <typename T> LSV_DEV T load_stream(const GLOBAL T* p) { return __builtin_nontemporal_load(p); }
 
+// 64 lanes x 16 bytes straight into LDS: lane l's piece goes to dst[l] (dst wave-uniform) from byte
+// voff + soff (soff wave-uniform).  The load counts as one outstanding vector-memory operation.
+template <int AUX> LSV_DEV void load_lds(__amdgpu_buffer_rsrc_t r, u32x4_t* dst, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)voff, (int)soff, 0, AUX);
+}
+// Wait until at most N vector-memory operations of this wave are outstanding (they retire in
+// order) and all of its LDS reads have returned.
+template <int N> LSV_DEV void wait_loads() {
+  static_assert(N >= 0 && N < 64, "six-bit counter");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);  // expcnt 7 (ignored), lgkmcnt 0
+}
+
 LSV_DEV float bf2f(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
 // fp32 -> bf16, round to nearest even; NaN stays a quiet NaN.

@@ -28,7 +28,7 @@ struct GemmArgs {
   // wide blocks: k-split partials [tiles][splits][M_max][128]
   float* part;
   size_t part_bytes;
-  int splits;
+  int splits, chunks;
   // EPI_LOGITS (and, for wide blocks, the normalised QKV projection before RoPE)
   float* out_f32;
   int ldo;
@@ -70,14 +70,15 @@ __host__ __device__ inline size_t split_pair_floats(int Nt, int M_max) {
   return (size_t)((Nt + 7) / 8) * 2 * M_max * 128;
 }
 
-// Batched blocks (bf16, 64 < rows <= kWideRows): every row in one workgroup, activations via LDS.
-constexpr int kWideRows = LSV_WIDE_ROWS;
+// Batched blocks (bf16, more than 64 rows): weights and activations via LDS, the rows in `chunks`
+// equal runs of whole 16-row tiles.
+constexpr int kWideOneChunk = 320;       // rows that every product takes in one chunk
 constexpr int kWideFR = 8;               // fragment rows of a batched workgroup's column tile
 constexpr int kWideCols = kWideFR * 16;  // its output columns: k-split partials are [tile][split][M_max][kWideCols]
 struct WidePlan {
-  int tiles, splits;
+  int tiles, splits, chunks;
 };
-WidePlan plan_wide(int Nt, int Kt);
+WidePlan plan_wide(int Nt, int Kt, int max_rows);
 size_t wide_part_floats(const WidePlan& p, int M_max);
 // Blocks under a batched bound: one launch whose workgroups take the 64-row body or the batched
 // one from the device row count (plus the batched body's reduce, which returns for <= 64 rows).

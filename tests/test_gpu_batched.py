@@ -1,5 +1,5 @@
-"""GPU verify at the batched shapes: more than 64 block rows, which the GEMMs process in
-64-row chunks and the attention in passes of query tiles.
+"""GPU verify at the batched shapes: more than 64 block rows, which take the GEMMs' batched body
+and the attention's passes of query tiles.
 
 * small bf16 model (d 1024, 8/2 x 128 heads), 8 sequences x 33 rows = 264 rows over
   ragged contexts;
@@ -79,3 +79,16 @@ def test_short_blocks_under_a_batched_bound():
     with 20 rows under 272."""
     _bf16_case(configs.LLAMA3_70B.with_layers(1), 24, [8192, 8100, 5000, 7000], [8, 8, 6, 6], bound=132)
     _bf16_case(configs.SMALL_BF16, 25, [300, 40, 129], [9, 5, 6], bound=272)
+
+
+@pytest.mark.parametrize("rows", [65, 128, 129, 257, 320, 321, 512])
+def test_batched_body_row_counts(rows):
+    """Row counts around the batched body's tilings (one to eight activation tiles per wave, one
+    chunk or two) on the tiny model, whose SwiGLU width of 688 ends in a k-block of six fragments."""
+    _bf16_case(configs.TINY_BF16, 26, [40, 7], [rows - 20, 20])
+
+
+def test_batched_body_rows_below_the_bound():
+    """A two-chunk plan (bound 512) with rows for one chunk and a part of the other, and for one only."""
+    _bf16_case(configs.TINY_BF16, 27, [40, 7], [80, 20], bound=512)
+    _bf16_case(configs.SMALL_BF16, 28, [40], [70], bound=512)
