@@ -344,17 +344,29 @@ __global__ void __launch_bounds__(256) embed_kernel(const T* __restrict__ E, int
                                                     T* a, const int32_t* tree_bad, int32_t* status) {
   const int m = blockIdx.x;
   if (m == 0 && status) {
-    for (int b = threadIdx.x; b < batch; b += blockDim.x) {
-      const int r0 = row_offsets[b], r1 = row_offsets[b + 1];
-      int st = LSV_OK;
-      if (r1 < r0 || seq_len[b] < 0 || seq_len[b] + (r1 - r0) > ctx_limit) st = LSV_ERR_CAPACITY;
-      if (r0 < 0 || r1 > M_max) {
-        status[b] = LSV_ERR_INVALID_ARG;
-        continue;
+    // 256 / batch threads per sequence share its rows
+    __shared__ int s_bad[LSV_MAX_BATCH];
+    const int t = threadIdx.x, per = 256 / batch, b = t / per;
+    if (t < batch) s_bad[t] = 0;
+    __syncthreads();
+    if (b < batch) {
+      const int r0 = GL(row_offsets)[b], r1 = GL(row_offsets)[b + 1];
+      if (r0 >= 0 && r1 <= M_max) {
+        int bad = 0;
+        for (int r = r0 + t % per; r < r1; r += per) {
+          const int tok = GL(tokens)[r];
+          bad |= tok < 0 || tok >= V || (tree_bad && GL(tree_bad)[r]);
+        }
+        if (bad) atomicOr(&s_bad[b], 1);
       }
-      for (int r = r0; r < r1; ++r)
-        if (tokens[r] < 0 || tokens[r] >= V || (tree_bad && tree_bad[r])) st = LSV_ERR_INVALID_ARG;
-      status[b] = st;
+    }
+    __syncthreads();
+    if (t < batch) {
+      const int r0 = row_offsets[t], r1 = row_offsets[t + 1], C = seq_len[t];
+      int st = LSV_OK;
+      if (r1 < r0 || C < 0 || C + (r1 - r0) > ctx_limit) st = LSV_ERR_CAPACITY;
+      if (r0 < 0 || r1 > M_max || s_bad[t]) st = LSV_ERR_INVALID_ARG;
+      status[t] = st;
     }
   }
   if (m >= GL(row_offsets)[batch] || m >= M_max) return;
