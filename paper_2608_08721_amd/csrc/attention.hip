@@ -45,14 +45,32 @@ constexpr int kComputeUnits = 256;  // gfx950 (MI350X, MI355X)
 // 11).  With every context at the bound, three rounds of a third of the length cost what one
 // round costs.  Split boundaries still follow from the host bound alone, so a row's result does
 // not depend on its block, its batch or the other sequences' lengths.
-AttnPlan plan_attention(int batch, int nkv, int max_ctx) {
+//
+// Blocks of many query tiles (prefill chunks, draft trees: four or more passes of the eight waves)
+// give every pass a workgroup of its own instead: query groups, not context splits, then fill the
+// chip, so a row has one or two partials instead of up to sixteen and a pass skips the chunks behind
+// its last row.  Llama-3-8B, 512 rows behind 1.5K positions: 16 splits walked by 128 workgroups in 16
+// passes each become 2 splits x 16 groups x 8 kv heads.  Such bounds are far above 64 rows, so the
+// bits of a row in blocks of up to 64 rows do not depend on it.
+AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int max_ctx) {
   const int n_chunks = (max_ctx + kCh - 1) / kCh;
-  const int units = batch * nkv;
+  const int tiles = ((max_rows + batch - 1) / batch * group + 15) / 16;  // per sequence, mean of the bound
+  int units = batch * nkv;
   int want = (kAttnWgs + units - 1) / units;
   const int by_length = (n_chunks + kMaxChunksPerSplit - 1) / kMaxChunksPerSplit;
   if (want < by_length) want = by_length;
   const int fit = kComputeUnits / units;  // splits per (sequence, kv head) in one round
   AttnPlan p;
+  p.q_groups = max_rows > 64 && tiles > 3 * 8 ? (tiles + 7) / 8 : 1;
+  if (p.q_groups > 1) {
+    units *= p.q_groups;
+    want = units < kComputeUnits ? kComputeUnits / units : 1;
+    if (want > n_chunks) want = n_chunks;
+    p.packed = 0;
+    p.chunks_per_split = (n_chunks + want - 1) / want;
+    p.n_splits = (n_chunks + p.chunks_per_split - 1) / p.chunks_per_split;
+    return p;
+  }
   p.packed = fit >= 1 && by_length > 2 * fit;
   if (p.packed)
     want = (by_length + fit - 1) / fit * fit;
@@ -125,7 +143,8 @@ __global__ void __launch_bounds__(64 * NW) attn_split_bf16_kernel(AttnArgs a) {
   __shared__ __align__(16) bf16_t Ks[NG][kCh * KPITCH];  // one chunk buffer per group
   __shared__ __align__(16) bf16_t Vt[NG][HD * VPITCH];
 
-  int s = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+  int s = blockIdx.x, kvh = blockIdx.y, b = (int)blockIdx.z / a.q_groups;
+  const int q_first = (int)blockIdx.z % a.q_groups * NW;  // packed grids have one query group
   if (a.packed && !packed_unit(a, blockIdx.x, s, kvh, b)) return;
   // the wave index in a scalar register: the group, its chunk offsets and the page-table reads
   // are then wave-uniform, and the buffer loads take their chunk offsets in scalar registers
@@ -201,14 +220,16 @@ __global__ void __launch_bounds__(64 * NW) attn_split_bf16_kernel(AttnArgs a) {
   const int group = a.nq / a.nkv, nqv = rows * group, n_qt = (nqv + 15) / 16;
   const int L = min(C + rows, a.ctx_limit);  // cached + block keys that exist
   const int nch = L > 0 ? (L + kCh - 1) / kCh : 0;
-  const int c1 = min(c0 + a.chunks_per_split, nch);
+  const int c1_all = min(c0 + a.chunks_per_split, nch);
   const size_t prow = (size_t)s * a.M_max + r0;  // this split's partial row of the sequence's first row
-  if (c0 >= c1) return;  // no key of this split exists for the sequence: the merge does not read it
+  if (c0 >= c1_all) return;  // no key of this split exists for the sequence: the merge does not read it
   // A pass over the split covers up to NW query tiles, one per wave, each wave running its
   // tile over all chunks in order.  Every tile takes the same chunk order and the same
   // arithmetic whatever the block's tile count, so a row's result does not depend on how
   // many rows share its block (decoding then emits the same tokens for every length).
-  for (int qbase = 0; qbase < n_qt; qbase += NW) {
+  for (int qbase = q_first; qbase < n_qt; qbase += NW * a.q_groups) {
+    // the chain's chunks behind the pass's last row hold no key that a row of it sees
+    const int c1 = a.anc ? c1_all : min(c1_all, (C + (min((qbase + NW) * 16, nqv) - 1) / group) / kCh + 1);
     const int qt = qbase + wave;
     const bool active = qt < n_qt;  // wave-uniform
     u32x4_t qf[HD / 32];
@@ -229,7 +250,7 @@ __global__ void __launch_bounds__(64 * NW) attn_split_bf16_kernel(AttnArgs a) {
 #pragma unroll
       for (int dt = 0; dt < HD / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    if (qbase > 0 && c0 + grp < c1) load_chunk(c0 + grp);  // a later pass over the same split
+    if (qbase > q_first && c0 + grp < c1) load_chunk(c0 + grp);  // a later pass over the same split
 
     // scores and running-softmax update of this wave's tile for the chunk in buffer g.
     // A chunk below the cached length C is visible to every row of the block: no mask, and
@@ -250,6 +271,20 @@ __global__ void __launch_bounds__(64 * NW) attn_split_bf16_kernel(AttnArgs a) {
                                                            __builtin_bit_cast(bf16x8_t, qf[ds]), sc[kt], 0, 0, 0);
         }
       }
+      // tree block: bit i of seen is key k0 + 4 g4 + i -- cached keys, then the slots of the row's
+      // ancestors and itself: the 64 mask bits from slot k0 - C on (three words; slots below 0 are
+      // cached keys, those past the last node hold none)
+      uint64_t seen = 0;
+      if (MASK && a.anc) {
+        const int j0 = k0 - C, w = j0 >> 5, sh = j0 & 31;
+        auto word = [&](int i) -> uint64_t {
+          if (i < 0) return 0xffffffffu;
+          return i < kAncWords ? GL(a.anc)[(size_t)(r0 + rr) * kAncWords + i] : 0u;
+        };
+        seen = (word(w) | word(w + 1) << 32) >> sh;
+        if (sh) seen |= word(w + 2) << (64 - sh);
+        seen >>= 4 * g4;
+      }
       // scale (log2 units), causal mask, running max over the split
       float mx = -INFINITY;
 #pragma unroll
@@ -260,10 +295,8 @@ __global__ void __launch_bounds__(64 * NW) attn_split_bf16_kernel(AttnArgs a) {
           if (MASK) {
             const int kp = k0 + 16 * kt + 4 * g4 + r;
             bool vis;
-            if (a.anc) {  // tree block: cached keys, then the slots of the row's ancestors and itself
-              const int j = kp - C;
-              vis = kp < C || (kp < L && j < kTreeNodes &&
-                               ((GL(a.anc)[(size_t)(r0 + rr) * kAncWords + (j >> 5)] >> (j & 31)) & 1u));
+            if (a.anc) {  // tree block
+              vis = ((seen >> (16 * kt + r)) & 1u) && kp < max(L, C);
             } else {
               vis = kp < L && kp <= qpos;
             }
@@ -461,7 +494,7 @@ __global__ void __launch_bounds__(64) attn_f32_kernel(AttnArgs a, int hd) {
 
 int launch_attention(int dtype, int hd, const AttnArgs& a, int max_rows, hipStream_t st) {
   if (dtype == LSV_DTYPE_BF16) {
-    const dim3 grid = a.packed ? dim3(a.n_splits * a.nkv * a.batch) : dim3(a.n_splits, a.nkv, a.batch);
+    const dim3 grid = a.packed ? dim3(a.n_splits * a.nkv * a.batch) : dim3(a.n_splits, a.nkv, a.batch * a.q_groups);
     const int hpw = 256 / hd;
     const dim3 mgrid(max_rows, (a.nq + hpw - 1) / hpw);
     // query tiles per sequence (rows of a single sequence, else the mean over the batch): up

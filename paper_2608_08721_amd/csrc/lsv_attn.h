@@ -60,6 +60,8 @@ struct AttnArgs {
   // packed grid (a 1-D grid of n_splits * nkv * batch workgroups): workgroup i takes the i-th
   // (sequence, kv head, split) that holds keys instead of blockIdx = (split, kv head, sequence)
   int packed;
+  // query groups: group g of a sequence's workgroups takes passes g, g + q_groups, ... over its tiles
+  int q_groups;
   // tree blocks: [M_max][kAncWords] ancestor-or-self masks; a block key (position >= the
   // cached length C) at slot C + j is visible to row m iff bit j of its mask is set.  NULL:
   // the causal block.
@@ -69,9 +71,9 @@ struct AttnArgs {
 // Split of the context into n_splits ranges of chunks_per_split chunks (bf16 path); packed:
 // the split kernel runs on a packed grid (AttnArgs::packed).
 struct AttnPlan {
-  int n_splits, chunks_per_split, packed;
+  int n_splits, chunks_per_split, packed, q_groups;
 };
-AttnPlan plan_attention(int batch, int nkv, int max_ctx);
+AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int max_ctx);
 
 int launch_attention(int dtype, int hd, const AttnArgs& a, int max_rows, hipStream_t st);
 
