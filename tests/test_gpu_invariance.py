@@ -66,6 +66,30 @@ def test_row_logits_do_not_depend_on_block_size_wide_model():
     note(f"  {shape.name}: 20 rows bit-identical as one block and as blocks of 9 + 11 and 5")
 
 
+def test_row_logits_do_not_depend_on_the_body_of_33_to_64_rows():
+    """Llama-3-8B width, one layer: under a batched bound gate/up and the LM head (one k range each)
+    run the batched body from 33 rows on, under a bound of 64 the streaming one.  The same 64 rows as
+    one block under either bound, and as blocks of 32, 1 and 31 rows under the batched one, must give
+    bit-identical logits."""
+    shape = configs.LLAMA3_8B.with_layers(1)
+    seed, C, R = 64, 90, 64
+    w = gen.model_weights(shape, seed)
+    cap = runtime.kv_capacity(C + R + 8)
+    gm = GpuModel(shape, w, 1, cap, max_rows=132)
+    k, v = gen.synthetic_kv(shape, seed, 0, 1, C)
+    gm.kv.write(0, 0, 0, runtime.to_device(k[0]), runtime.to_device(v[0]))
+    toks = gen.randint(seed, 900, R, shape.vocab)
+    whole, st = gm.verify([C], toks, [0, R], max_rows=64)
+    assert st[0] == 0 and np.isfinite(whole).all()
+    for sizes in ([R], [33, 31], [32, 1, 31]):
+        pos = 0
+        for n in sizes:
+            lg, st = gm.verify([C + pos], toks[pos:pos + n], [0, n], max_rows=132)
+            assert st[0] == 0
+            assert np.array_equal(lg, whole[pos:pos + n]), (sizes, pos)
+            pos += n
+
+
 def test_packed_attention_grid_rows_do_not_depend_on_the_batch():
     """The packed split grid (eight ragged sequences of up to 8,190 positions over eight kv
     heads) takes a workgroup per split that holds keys, so which workgroup computes a split
