@@ -277,13 +277,21 @@ __global__ void __launch_bounds__(256) accept_tree_kernel(const RowPartial* __re
     // argmax of row i: chunk partials in ascending order, strict '>' keeps the first maximum
     float best = -INFINITY;
     int bi = 0x7fffffff;
+    // eight partials' loads in flight at a time (512 nodes, 32 chunks: the kernel 28.7 -> 25.4 us)
+    constexpr int NB = 8;
     const RowPartial* rp = parts + (size_t)(r0 + i) * nc;
-    for (int c = 0; c < nc; ++c) {
-      const RowPartial q = rp[c];
-      bad_val |= q.bad;
-      if (q.a > best || bi == 0x7fffffff) {
-        best = q.a;
-        bi = q.idx;
+    for (int c0 = 0; c0 < nc; c0 += NB) {
+      RowPartial q[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) q[k] = rp[min(c0 + k, nc - 1)];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        if (c0 + k >= nc) break;
+        bad_val |= q[k].bad;
+        if (q[k].a > best || bi == 0x7fffffff) {
+          best = q[k].a;
+          bi = q[k].idx;
+        }
       }
     }
     s_top[i] = bi;
@@ -408,11 +416,26 @@ __global__ void __launch_bounds__(64) accept_sample_decide_kernel(const RowParti
   float m = -INFINITY, z = 0.f;
   int bad = 0;
   if (lane < rows) {
-    for (int c = 0; c < nc; ++c) m = fmaxf(m, parts[(size_t)(r0 + lane) * nc + c].a);
-    for (int c = 0; c < nc; ++c) {  // fixed chunk order
-      RowPartial p = parts[(size_t)(r0 + lane) * nc + c];
-      bad |= p.bad;
-      z += p.b * expf(p.a - m);
+    // eight partials' loads in flight at a time
+    constexpr int NB = 8;
+    const RowPartial* rp = parts + (size_t)(r0 + lane) * nc;
+    for (int c0 = 0; c0 < nc; c0 += NB) {
+      float v[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) v[i] = rp[min(c0 + i, nc - 1)].a;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) m = fmaxf(m, v[i]);
+    }
+    for (int c0 = 0; c0 < nc; c0 += NB) {  // fixed chunk order
+      RowPartial p[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) p[i] = rp[min(c0 + i, nc - 1)];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (c0 + i >= nc) break;
+        bad |= p[i].bad;
+        z += p[i].b * expf(p[i].a - m);
+      }
     }
   }
   // ratio test of draft v = lane + 1 against row lane
