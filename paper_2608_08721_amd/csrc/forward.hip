@@ -348,7 +348,8 @@ __global__ void __launch_bounds__(256) embed_kernel(const T* __restrict__ E, int
                                                     T* a, const int32_t* tree_bad, int32_t* status) {
   const int m = blockIdx.x;
   if (m == 0 && status) {
-    // 256 / batch threads per sequence share its rows
+    // 256 / batch threads per sequence share its rows (one thread per sequence walked 512 rows of one
+    // sequence in 74 us of dependent loads, 104 us for a tree; the whole kernel now takes 16 us)
     __shared__ int s_bad[LSV_MAX_BATCH];
     const int t = threadIdx.x, per = 256 / batch, b = t / per;
     if (t < batch) s_bad[t] = 0;
