@@ -85,6 +85,17 @@ def test_attention_split_plan_in_the_workspace_size(lib):
     assert ws(4, 129 * 64) == ws(4, 128 * 64)
 
 
+def test_a_workspace_serves_every_smaller_row_bound(lib):
+    """The plans change with the row bound (two row chunks above 320 rows, query groups in the
+    attention), each with fewer partials per row; the workspace must still grow with the bound."""
+    for d, nq, nkv, hd, ff in ((1024, 8, 2, 128, 2816), (4096, 32, 8, 128, 14336)):
+        cfg = tiny_cfg(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ff=ff, vocab=4096,
+                       dtype=lsv.LSV_DTYPE_BF16)
+        for batch in (1, 4):
+            sizes = [lsv.lsv_verify_workspace_bytes(cfg, batch, rows, 2048) for rows in range(1, lsv.LSV_MAX_ROWS + 1)]
+            assert sizes == sorted(sizes)
+
+
 def expect(code, fn, *args):
     with pytest.raises(lsv.LsvError) as e:
         fn(*args)
