@@ -11,6 +11,8 @@ and the attention's passes of query tiles.
 
 Logits bar: each row within 2e-2 of its largest |logit| (bf16 operands, fp32 accumulation);
 greedy decisions equal wherever the oracle's top-2 margin clears twice the error."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -92,3 +94,24 @@ def test_batched_body_rows_below_the_bound():
     """A two-chunk plan (bound 512) with rows for one chunk and a part of the other, and for one only."""
     _bf16_case(configs.TINY_BF16, 27, [40, 7], [80, 20], bound=512)
     _bf16_case(configs.SMALL_BF16, 28, [40], [70], bound=512)
+
+
+def test_query_groups_lose_no_precision():
+    """512 rows of one sequence behind 2,100 positions as one block, whose query tiles the attention
+    takes in groups over one or two long splits, and as eight blocks of 64 rows over fourteen short
+    ones.  The probabilities are rounded to bf16 either way, so the block may stand no further off
+    the oracle's float64 than the short blocks do.  Row errors scatter by some 4%, so the norm over
+    512 rows by 0.2%, and the two errors share most of their roundings: a bar of 0.5% (equal splits
+    read 1.0001; a maximum kept over a group's whole split reads 1.0104)."""
+    shape = dataclasses.replace(configs.SMALL_BF16, n_q_heads=32, n_kv_heads=8, n_layers=1, name="small-bf16-32-8")
+    seed, C, R = 29, 2100, lsv.LSV_MAX_ROWS
+    gm, whole, want, toks, off = _bf16_case(shape, seed, [C], [R], bound=R)
+    short = []
+    for pos in range(0, R, 64):
+        lg, st = gm.verify([C + pos], toks[pos:pos + 64], [0, 64], max_rows=64)
+        assert st[0] == 0
+        short.append(lg)
+    scale = np.linalg.norm(want)
+    e_whole, e_short = np.linalg.norm(whole - want) / scale, np.linalg.norm(np.concatenate(short) - want) / scale
+    note(f"  512 rows off float64: {e_whole:.3e} as one block, {e_short:.3e} as blocks of 64 ({e_whole / e_short:.4f})")
+    assert e_whole <= 1.005 * e_short
