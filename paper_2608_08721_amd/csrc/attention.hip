@@ -2,7 +2,7 @@
 //
 // bf16 path (matrix cores), two kernels:
 //  * split kernel: one workgroup of four or eight waves per (context split, kv head,
-//    sequence).  A split is a run of 64-key chunks.  Each chunk's K rows and transposed V
+//    sequence), and per query group of sequences with many rows (lsv_attn_plan.h).  A split is a run of 64-key chunks.  Each chunk's K rows and transposed V
 //    rows (a contiguous [64][hd] and [hd][64] block per chunk, next to the other kv heads'
 //    blocks) go HBM -> registers -> LDS with 16-byte accesses; the first chunk's loads are issued before any device metadata is read, and
 //    each next chunk's loads are in flight while the current one is consumed.  A wave owns one tile of 16 query vectors (block
@@ -24,116 +24,70 @@
 namespace lsv {
 
 constexpr int kCh = kAttnChunk;  // keys per chunk
-// Split plan: about kAttnWgs split workgroups, and no split longer than kMaxChunksPerSplit
-// chunks (a split walks its chunks in sequence).  Fewer splits mean fewer partials to merge
-// -- one batch of merge loads for up to 16 -- against longer chunk walks; 128 measured best
-// for one sequence of 2K context (11 splits of 3 chunks).  The length cap keeps the
-// workgroups of a batch with long contexts from running too long -- but never beyond one
-// workgroup per compute unit: a grid larger than the chip runs its last workgroups in a
-// second round, which costs more than longer splits (Llama-3-70B, four sequences of 8K
-// context: 9 splits, 288 workgroups, 49 us; 8 splits, 256 workgroups, 34 us).
-constexpr int kAttnWgs = 128;
-constexpr int kMaxChunksPerSplit = 16;
-constexpr int kComputeUnits = 256;  // gfx950 (MI350X, MI355X)
 
-//
-// Long contexts over many (sequence, kv head) pairs -- when one round's splits would walk more
-// than twice the length cap -- take a whole number of rounds' worth of splits instead, on a
-// packed grid: the splits that hold keys come first, so in a batch of ragged contexts the
-// empty splits of the short sequences no longer hold compute units while a long sequence walks
-// its splits (Llama-3-8B, batch 8, contexts of 1.7K-8.2K: 4 splits of 33 chunks become 12 of
-// 11).  With every context at the bound, three rounds of a third of the length cost what one
-// round costs.  Split boundaries still follow from the host bound alone, so a row's result does
-// not depend on its block, its batch or the other sequences' lengths.
-//
-// Blocks of many query tiles (prefill chunks, draft trees: four or more passes of the eight waves)
-// give every pass a workgroup of its own instead: query groups, not context splits, then fill the
-// chip, so a row has one or two partials instead of up to sixteen and a pass skips the chunks behind
-// its last row.  Llama-3-8B, 512 rows behind 1.5K positions: 16 splits walked by 128 workgroups in 16
-// passes each become 2 splits x 16 groups x 8 kv heads.  Such bounds are far above 64 rows, so the
-// bits of a row in blocks of up to 64 rows do not depend on it.
-AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int max_ctx) {
-  const int n_chunks = (max_ctx + kCh - 1) / kCh;
-  const int tiles = ((max_rows + batch - 1) / batch * group + 15) / 16;  // per sequence, mean of the bound
-  int units = batch * nkv;
-  int want = (kAttnWgs + units - 1) / units;
-  const int by_length = (n_chunks + kMaxChunksPerSplit - 1) / kMaxChunksPerSplit;
-  if (want < by_length) want = by_length;
-  const int fit = kComputeUnits / units;  // splits per (sequence, kv head) in one round
-  AttnPlan p;
-  p.q_groups = max_rows > 64 && tiles > 3 * 8 ? (tiles + 7) / 8 : 1;
-  if (p.q_groups > 1) {
-    units *= p.q_groups;
-    want = units < kComputeUnits ? kComputeUnits / units : 1;
-    if (want > n_chunks) want = n_chunks;
-    p.packed = 0;
-    p.chunks_per_split = (n_chunks + want - 1) / want;
-    p.n_splits = (n_chunks + p.chunks_per_split - 1) / p.chunks_per_split;
-    return p;
-  }
-  p.packed = fit >= 1 && by_length > 2 * fit;
-  if (p.packed)
-    want = (by_length + fit - 1) / fit * fit;
-  else if (want > fit)
-    want = fit;
-  if (want > n_chunks) want = n_chunks;
-  if (want < 1) want = 1;
-  p.chunks_per_split = (n_chunks + want - 1) / want;
-  p.n_splits = (n_chunks + p.chunks_per_split - 1) / p.chunks_per_split;
-  return p;
+// The plan of the sequence that owns rows r0 .. r1 - 1; no split where they are not all below the host
+// bound.  GROUPED: plans with query groups.
+template <bool GROUPED>
+LSV_DEV SeqPlan plan_of(const AttnArgs& a, int r0, int r1, int C, int M) {
+  const int rows = r0 < 0 || r1 > a.M_max ? 0 : r1 - r0;
+  if (GROUPED) return seq_plan(a.plan, a.batch, a.nkv, a.ctx_limit, rows, C, M);
+  return SeqPlan{splits_with_keys(a.plan.chunks_per_split, a.ctx_limit, rows, C), a.plan.chunks_per_split, 1};
 }
 
-// Splits of sequence b that hold keys: ceil(chunks / chunks_per_split), none for a sequence
-// without rows (or rows past the host bound).  At most n_splits, since L <= ctx_limit.
-LSV_DEV int active_splits(const AttnArgs& a, int r0, int rows, int C) {
-  if (r0 < 0 || rows <= 0 || r0 + rows > a.M_max) return 0;
-  const int L = min(C + rows, a.ctx_limit);
-  const int nch = L > 0 ? (L + kCh - 1) / kCh : 0;
-  return (nch + a.chunks_per_split - 1) / a.chunks_per_split;
-}
+// What a workgroup of the split kernel takes: split s of kv head kvh of sequence b, `chunks` chunks a
+// split, and group g of `groups` of its query tiles.
+struct SplitUnit {
+  int s, kvh, b, chunks, g, groups;
+};
 
 // Packed grid: workgroup i takes the i-th split that holds keys -- every sequence's full splits
-// first (ordered by sequence, split, kv head), then every sequence's last split (by sequence, kv
-// head) -- so the longest splits start first.  One lane per sequence (batch <= 64); every wave
-// computes the same answer, moved to scalar registers.  False: no split is left for i.
-LSV_DEV bool packed_unit(const AttnArgs& a, int i, int& s, int& kvh, int& b) {
+// first (ordered by sequence, query group, split, kv head), then every sequence's last split (by
+// sequence, query group, kv head) -- so the longest splits start first.  One lane per sequence
+// (batch <= 64); every wave computes the same answer, moved to scalar registers.  False: no split is
+// left for i.
+template <bool GROUPED>
+LSV_DEV bool packed_unit(const AttnArgs& a, int i, SplitUnit& u) {
   const int lane = threadIdx.x & 63;
-  int act = 0;
-  if (lane < a.batch) {
-    const int r0 = GL(a.row_offsets)[lane], r1 = GL(a.row_offsets)[lane + 1];
-    act = active_splits(a, r0, r1 - r0, GL(a.seq_len)[lane]);
-  }
-  const int full = act > 0 ? (act - 1) * a.nkv : 0, last = act > 0 ? a.nkv : 0;
+  SeqPlan p{0, 1, 1};
+  if (lane < a.batch)
+    p = plan_of<GROUPED>(a, GL(a.row_offsets)[lane], GL(a.row_offsets)[lane + 1], GL(a.seq_len)[lane],
+                         GL(a.row_offsets)[a.batch]);
+  const int last = p.splits > 0 ? a.nkv * p.groups : 0, full = p.splits > 0 ? (p.splits - 1) * last : 0;
   int pf = full, pl = last;  // inclusive prefix sums over the lanes
-  for (int o = 1; o < kWave; o <<= 1) {
+  for (int o = 1; o < a.batch; o <<= 1) {
     const int tf = __shfl_up(pf, o, kWave), tl = __shfl_up(pl, o, kWave);
     if (lane >= o) {
       pf += tf;
       pl += tl;
     }
   }
-  const int F = __builtin_amdgcn_readfirstlane(__shfl(pf, kWave - 1, kWave));
-  const int P = __builtin_amdgcn_readfirstlane(__shfl(pl, kWave - 1, kWave));
+  const int F = __builtin_amdgcn_readlane(pf, a.batch - 1);
+  const int P = __builtin_amdgcn_readlane(pl, a.batch - 1);
   const bool in_full = i < F;
   const int j = in_full ? i : i - F;
   if (!in_full && j >= P) return false;
   const unsigned long long over = __ballot(in_full ? pf > j : pl > j);  // lanes past unit j
   const int bb = __builtin_amdgcn_readfirstlane(__ffsll((long long)over) - 1);
-  const int local = j - __builtin_amdgcn_readfirstlane(__shfl(in_full ? pf - full : pl - last, bb, kWave));
-  b = bb;
-  if (in_full) {
-    s = local / a.nkv;
-    kvh = local % a.nkv;
-  } else {
-    s = __builtin_amdgcn_readfirstlane(__shfl(act, bb, kWave)) - 1;
-    kvh = local;
+  const int local = j - __builtin_amdgcn_readlane(in_full ? pf - full : pl - last, bb);
+  const int splits = __builtin_amdgcn_readlane(p.splits, bb);
+  u.b = bb;
+  if (!GROUPED) {
+    u.s = in_full ? local / a.nkv : splits - 1;
+    u.kvh = in_full ? local % a.nkv : local;
+    return true;
   }
+  u.chunks = __builtin_amdgcn_readlane(p.chunks, bb);
+  u.groups = __builtin_amdgcn_readlane(p.groups, bb);
+  u.kvh = local % a.nkv;
+  const int t = local / a.nkv;
+  u.g = in_full ? t / (splits - 1) : t;
+  u.s = in_full ? t % (splits - 1) : splits - 1;
   return true;
 }
 
 // Registers are held to two waves per SIMD at head dimension 128 and four at 64: left to itself the
 // compiler takes 276 and 160 in the four-wave kernel (Llama-3-8B, 32 paged sequences: 1502 -> 1549 us).
-// GROUPED: plans with query groups.
+// Plans with query groups (GROUPED) have eight waves: more than kGroupTiles query tiles.
 template <int HD, int NW, bool GROUPED = false>
 __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_kernel(AttnArgs a) {
   constexpr int NG = NW / 4;               // wave groups: each loads one chunk per step
@@ -146,9 +100,13 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
   __shared__ __align__(16) bf16_t Ks[NG][kCh * KPITCH];  // one chunk buffer per group
   __shared__ __align__(16) bf16_t Vt[NG][HD * VPITCH];
 
-  int s = blockIdx.x, kvh = blockIdx.y, b = (int)blockIdx.z / a.q_groups;
-  const int q_first = (int)blockIdx.z % a.q_groups * NW;  // packed grids have one query group
-  if (a.packed && !packed_unit(a, blockIdx.x, s, kvh, b)) return;
+  SplitUnit unit{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, a.plan.chunks_per_split, 0, 1};
+  if (a.plan.packed && !packed_unit<GROUPED>(a, blockIdx.x, unit)) return;
+  const int s = unit.s, kvh = unit.kvh, b = unit.b;
+  // left to run time: as constants they make the compiler peel the first pass, which was slower
+  // (Llama-3-8B, 8 x 33 rows, six layers: 2139 -> 2194 us)
+  int q_first = unit.g * NW, q_step = unit.groups * NW;
+  asm("" : "+s"(q_first), "+s"(q_step));
   // the wave index in a scalar register: the group, its chunk offsets and the page-table reads
   // are then wave-uniform, and the buffer loads take their chunk offsets in scalar registers
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -159,7 +117,7 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
   // capacity / kCh is one of the sequence's blocks.  Paged mode: a chunk is a page; chunks
   // below max_pages have a page-table entry.
   const bool paged = a.kv.pages != nullptr;
-  const int c0 = s * a.chunks_per_split, cap_chunks = paged ? a.kv.max_pages : a.capacity / kCh;
+  const int c0 = s * unit.chunks, cap_chunks = paged ? a.kv.max_pages : a.capacity / kCh;
 
   // a step covers chunks c .. c+NG-1, group g loading chunk c+g into buffer g; the next
   // step's chunks are in flight in registers while the current ones are used. The loads go
@@ -216,22 +174,22 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
       *(u32x4_t*)&Vt[grp][(i >> 3) * VPITCH + (i & 7) * 8] = vr[j];
     }
   };
-  if (grp < a.chunks_per_split && c0 + grp < cap_chunks) load_chunk(c0 + grp);
+  if (grp < unit.chunks && c0 + grp < cap_chunks) load_chunk(c0 + grp);
 
   const int r0 = GL(a.row_offsets)[b], rows = GL(a.row_offsets)[b + 1] - r0, C = GL(a.seq_len)[b];
   if (r0 < 0 || rows <= 0 || r0 + rows > a.M_max) return;  // rows beyond the host bound are never touched
   const int group = a.nq / a.nkv, nqv = rows * group, n_qt = (nqv + 15) / 16;
   const int L = min(C + rows, a.ctx_limit);  // cached + block keys that exist
   const int nch = L > 0 ? (L + kCh - 1) / kCh : 0;
-  const int c1_all = min(c0 + a.chunks_per_split, nch);
+  const int c1_all = min(c0 + unit.chunks, nch);
   const size_t prow = (size_t)s * a.M_max + r0;  // this split's partial row of the sequence's first row
   if (c0 >= c1_all) return;  // no key of this split exists for the sequence: the merge does not read it
-  constexpr bool local = GROUPED;  // chunk maxima (see consume)
+  const bool local = GROUPED && unit.groups > 1;  // chunk maxima (see consume)
   // A pass over the split covers up to NW query tiles, one per wave, each wave running its
   // tile over all chunks in order.  Every tile takes the same chunk order and the same
   // arithmetic whatever the block's tile count, so a row's result does not depend on how
   // many rows share its block (decoding then emits the same tokens for every length).
-  for (int qbase = q_first; qbase < n_qt; qbase += NW * a.q_groups) {
+  for (int qbase = q_first; qbase < n_qt; qbase += q_step) {
     // the chain's chunks behind the pass's last row hold no key that a row of it sees
     const int c1 = a.anc ? c1_all : min(c1_all, (C + (min((qbase + NW) * 16, nqv) - 1) / group) / kCh + 1);
     const int qt = qbase + wave;
@@ -272,9 +230,9 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
     // every chunk is then exact; under the running maximum only those are that raise it, which is
     // few of them in a group's one or two long splits (Llama-3-8B width, one layer, a tree of 512
     // rows: 5.36e-3 off float64 with the running maximum, 5.18e-3 over eleven short splits, 5.08e-3
-    // with chunk maxima, for about 5 us of a layer's 380).
-    auto consume = [&](int g, int c, auto masked) {
-      constexpr bool MASK = decltype(masked)::value;
+    // with chunk maxima, for 2 to 3 us of a layer's 380).
+    auto consume = [&](int g, int c, auto masked, auto chunk_max) {
+      constexpr bool MASK = decltype(masked)::value, LOCAL = decltype(chunk_max)::value;
       const int k0 = c * kCh;
       f32x4_t sc[4];
 #pragma unroll
@@ -324,7 +282,7 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
       mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
       mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
       const float mnew = fmaxf(mrun, mx);
-      const float ref = local ? mx : mnew;
+      const float ref = LOCAL ? mx : mnew;
       float alpha, sum = 0.f;
       if (MASK) {
         alpha = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mnew);
@@ -350,9 +308,10 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
       sum += __shfl_xor(sum, 16, kWave);
       sum += __shfl_xor(sum, 32, kWave);
       mrun = mnew;
-      if (local) {
+      if constexpr (LOCAL) {
         const float beta = MASK && mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - mnew);
         lrun = lrun * alpha + sum * beta;
+        f32x4_t t[HD / 16];
         bf16x8_t pb[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
@@ -363,11 +322,16 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
           }
 #pragma unroll
         for (int dt = 0; dt < HD / 16; ++dt) {
-          f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+          t[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) t = mfma_pv(g, dt, ks, pb[ks], t);
-          o[dt] = o[dt] * alpha + t * beta;
+          for (int ks = 0; ks < 2; ++ks) t[dt] = mfma_pv(g, dt, ks, pb[ks], t[dt]);
         }
+        if (!__all(alpha == 1.f)) {  // few chunks of a long split raise a row's maximum
+#pragma unroll
+          for (int dt = 0; dt < HD / 16; ++dt) o[dt] *= alpha;
+        }
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_elementwise_fma(t[dt], f32x4_t{beta, beta, beta, beta}, o[dt]);
         return;
       }
       lrun = lrun * alpha + sum;
@@ -392,13 +356,19 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
       __syncthreads();
       if (c + NG + grp < c1) load_chunk(c + NG + grp);
       if (!active) continue;  // wave-uniform: a wave without a query tile in this pass
-      using Masked = std::true_type;
-      using Full = std::false_type;
+      using Yes = std::true_type;
+      using No = std::false_type;
 #pragma unroll
       for (int g = 0; g < NG; ++g)
         if (c + g < c1) {
-          if ((c + g + 1) * kCh <= C) consume(g, c + g, Full{});
-          else consume(g, c + g, Masked{});
+          const bool full = (c + g + 1) * kCh <= C;
+          if (local) {
+            if (full) consume(g, c + g, No{}, std::bool_constant<GROUPED>{});
+            else consume(g, c + g, Yes{}, std::bool_constant<GROUPED>{});
+          } else {
+            if (full) consume(g, c + g, No{}, No{});
+            else consume(g, c + g, Yes{}, No{});
+          }
         }
     }
 
@@ -414,29 +384,11 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
 }
 
 // Merge the split partials of one (row, query head): out = sum_s w_s o_s / sum_s w_s l_s,
-// w_s = 2^(m_s - max_s m_s), splits in ascending order, NB splits' loads in flight at a time.
-// Only the splits that hold keys of the row's sequence were written and are read.
-// A wave covers 256 / HD heads of one row, four head dimensions per lane.
-// NB: splits' loads in flight at a time, a power of two at least n_splits up to 16 (the loads past
-// a row's last split repeat it, so a plan of two splits would load each sixteen-fold with NB 16); a
-// row whose splits fit one batch has the same bits under any NB.
+// w_s = 2^(m_s - max_s m_s), splits in ascending order, NB splits' loads in flight at a time: a power
+// of two at least ns up to 16 (the loads past a row's last split repeat it, so two splits would load
+// each sixteen-fold with NB 16); a row whose splits fit one batch has the same bits under any NB.
 template <int HD, int NB>
-__global__ void __launch_bounds__(64) attn_merge_bf16_kernel(AttnArgs a) {
-  constexpr int LPH = HD / 4, HPW = 64 / LPH;
-  const int m = blockIdx.x, head = blockIdx.y * HPW + threadIdx.x / LPH, d = (threadIdx.x % LPH) * 4;
-  // lane t: sequence t (batch <= 64); the row's sequence is the number of sequences ending at
-  // or before it
-  int mr0 = 0, mr1 = 0, mC = 0;
-  if ((int)threadIdx.x < a.batch) {
-    mr0 = GL(a.row_offsets)[threadIdx.x];
-    mr1 = GL(a.row_offsets)[threadIdx.x + 1];
-    mC = GL(a.seq_len)[threadIdx.x];
-  }
-  const int M = __shfl(mr1, a.batch - 1, kWave);
-  const int b = __popcll(__ballot((int)threadIdx.x < a.batch && mr1 <= m));
-  const int r0 = __shfl(mr0, b, kWave), r1 = __shfl(mr1, b, kWave), C = __shfl(mC, b, kWave);
-  if (m >= M || head >= a.nq) return;  // after the lane exchanges, which need every lane
-  const int ns = active_splits(a, r0, r1 - r0, C);
+LSV_DEV void merge_splits(const AttnArgs& a, int m, int head, int d, int ns) {
   const size_t stride = (size_t)a.M_max * a.nq, rh = (size_t)m * a.nq + head;
   const GLOBAL f32x2_t* ml = (const GLOBAL f32x2_t*)a.ml_part;
   const GLOBAL float* op = GL(a.o_part);
@@ -474,6 +426,34 @@ __global__ void __launch_bounds__(64) attn_merge_bf16_kernel(AttnArgs a) {
                           (uint32_t)f2bf(r[2]) | ((uint32_t)f2bf(r[3]) << 16)};
   // the O projection's activation operand: column head * HD + d of row m (d .. d+3 adjacent)
   *(GLOBAL u32x2_t*)(GL((bf16_t*)a.out) + act_index<32>(m, head * HD + d, a.nq * HD / 32)) = packed;
+}
+
+// Only the splits that hold keys of the row's sequence were written and are read.
+// A wave covers 256 / HD heads of one row, four head dimensions per lane.
+// GROUPED: sequences in query groups have fewer splits than the plan's.
+template <int HD, int NB, bool GROUPED>
+__global__ void __launch_bounds__(64) attn_merge_bf16_kernel(AttnArgs a) {
+  constexpr int LPH = HD / 4, HPW = 64 / LPH;
+  const int m = blockIdx.x, head = blockIdx.y * HPW + threadIdx.x / LPH, d = (threadIdx.x % LPH) * 4;
+  // lane t: sequence t (batch <= 64); the row's sequence is the number of sequences ending at
+  // or before it
+  int mr0 = 0, mr1 = 0, mC = 0;
+  if ((int)threadIdx.x < a.batch) {
+    mr0 = GL(a.row_offsets)[threadIdx.x];
+    mr1 = GL(a.row_offsets)[threadIdx.x + 1];
+    mC = GL(a.seq_len)[threadIdx.x];
+  }
+  const int M = __shfl(mr1, a.batch - 1, kWave);
+  const int b = __popcll(__ballot((int)threadIdx.x < a.batch && mr1 <= m));
+  const int r0 = __shfl(mr0, b, kWave), r1 = __shfl(mr1, b, kWave), C = __shfl(mC, b, kWave);
+  if (m >= M || head >= a.nq) return;  // after the lane exchanges, which need every lane
+  const int ns = plan_of<GROUPED>(a, r0, r1, C, M).splits;
+  if (GROUPED && NB > 2 && ns <= 2)
+    merge_splits<HD, 2>(a, m, head, d, ns);
+  else if (GROUPED && NB > 8 && ns <= 8)
+    merge_splits<HD, 8>(a, m, head, d, ns);
+  else
+    merge_splits<HD, NB>(a, m, head, d, ns);
 }
 
 // fp32 path: one wave per (row, query head); scores in LDS.
@@ -529,19 +509,19 @@ __global__ void __launch_bounds__(64) attn_f32_kernel(AttnArgs a, int hd) {
   }
 }
 
-template <int HD>
+template <int HD, bool GROUPED>
 static void launch_merge(dim3 grid, const AttnArgs& a, hipStream_t st) {
-  if (a.n_splits <= 2)
-    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 2>), grid, dim3(64), 0, st, a);
-  else if (a.n_splits <= 8)
-    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 8>), grid, dim3(64), 0, st, a);
+  if (a.plan.n_splits <= 2)
+    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 2, GROUPED>), grid, dim3(64), 0, st, a);
+  else if (a.plan.n_splits <= 8)
+    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 8, GROUPED>), grid, dim3(64), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 16>), grid, dim3(64), 0, st, a);
+    hipLaunchKernelGGL((attn_merge_bf16_kernel<HD, 16, GROUPED>), grid, dim3(64), 0, st, a);
 }
 
 int launch_attention(int dtype, int hd, const AttnArgs& a, int max_rows, hipStream_t st) {
   if (dtype == LSV_DTYPE_BF16) {
-    const dim3 grid = a.packed ? dim3(a.n_splits * a.nkv * a.batch) : dim3(a.n_splits, a.nkv, a.batch * a.q_groups);
+    const dim3 grid = a.plan.packed ? dim3(a.plan.n_wgs) : dim3(a.plan.n_splits, a.nkv, a.batch);
     const int hpw = 256 / hd;
     const dim3 mgrid(max_rows, (a.nq + hpw - 1) / hpw);
     // query tiles per sequence (rows of a single sequence, else the mean over the batch): up
@@ -549,21 +529,21 @@ int launch_attention(int dtype, int hd, const AttnArgs& a, int max_rows, hipStre
     const int rows_seq = (max_rows + a.batch - 1) / a.batch;
     const bool wide = (size_t)rows_seq * (a.nq / a.nkv) > 64;
     if (hd == 128) {
-      if (a.q_groups > 1)
+      if (a.plan.grouped)
         hipLaunchKernelGGL((attn_split_bf16_kernel<128, 8, true>), grid, dim3(512), 0, st, a);
       else if (wide)
         hipLaunchKernelGGL((attn_split_bf16_kernel<128, 8>), grid, dim3(512), 0, st, a);
       else
         hipLaunchKernelGGL((attn_split_bf16_kernel<128, 4>), grid, dim3(256), 0, st, a);
-      launch_merge<128>(mgrid, a, st);
+      a.plan.grouped ? launch_merge<128, true>(mgrid, a, st) : launch_merge<128, false>(mgrid, a, st);
     } else if (hd == 64) {
-      if (a.q_groups > 1)
+      if (a.plan.grouped)
         hipLaunchKernelGGL((attn_split_bf16_kernel<64, 8, true>), grid, dim3(512), 0, st, a);
       else if (wide)
         hipLaunchKernelGGL((attn_split_bf16_kernel<64, 8>), grid, dim3(512), 0, st, a);
       else
         hipLaunchKernelGGL((attn_split_bf16_kernel<64, 4>), grid, dim3(256), 0, st, a);
-      launch_merge<64>(mgrid, a, st);
+      a.plan.grouped ? launch_merge<64, true>(mgrid, a, st) : launch_merge<64, false>(mgrid, a, st);
     } else {
       return LSV_ERR_UNSUPPORTED;
     }

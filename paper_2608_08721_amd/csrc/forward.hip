@@ -95,7 +95,6 @@ struct VerifyPlan {
   WidePlan w[5];
   size_t part_floats;
   AttnPlan attn;
-  int attn_splits;  // that the partial buffers hold
 };
 
 static VerifyPlan plan_verify(const Shape& s, const ModelLayout& ml, int batch, int max_rows, int max_ctx) {
@@ -118,9 +117,6 @@ static VerifyPlan plan_verify(const Shape& s, const ModelLayout& ml, int batch, 
     }
   }
   v.attn = plan_attention(batch, s.nkv, s.nq / s.nkv, max_rows, max_ctx);
-  // a workspace serves every smaller row bound too, also one without query groups (more splits)
-  v.attn_splits = plan_attention(batch, s.nkv, s.nq / s.nkv, 1, max_ctx).n_splits;
-  if (v.attn_splits < v.attn.n_splits) v.attn_splits = v.attn.n_splits;
   return v;
 }
 
@@ -143,8 +139,8 @@ static VerifyWs carve_verify(const Shape& s, const ModelLayout& ml, const Verify
   w.attn = take(act_bytes(s.nq * s.hd));
   w.u = take(act_bytes(s.F));
   if (s.dtype == LSV_DTYPE_BF16) {
-    w.o_part = (float*)take(sizeof(float) * (size_t)v.attn_splits * max_rows * s.nq * s.hd);
-    w.ml_part = (float*)take(sizeof(float) * (size_t)v.attn_splits * max_rows * s.nq * 2);
+    w.o_part = (float*)take(sizeof(float) * (size_t)v.attn.n_splits * max_rows * s.nq * s.hd);
+    w.ml_part = (float*)take(sizeof(float) * (size_t)v.attn.n_splits * max_rows * s.nq * 2);
   } else {
     w.o_part = w.ml_part = nullptr;
   }
@@ -502,10 +498,7 @@ int launch_verify(const Shape& s, const ModelLayout& ml, const void* packed, voi
     at.ml_part = w.ml_part;
     at.out = w.attn;
     at.scale_log2 = (float)(1.4426950408889634 / sqrt((double)s.hd));
-    at.n_splits = v.attn.n_splits;
-    at.chunks_per_split = v.attn.chunks_per_split;
-    at.packed = v.attn.packed;
-    at.q_groups = v.attn.q_groups;
+    at.plan = v.attn;
     at.anc = parents ? w.anc : nullptr;
     timing_before(LSV_KERNEL_ATTENTION, l, st);
     if ((rc = launch_attention(s.dtype, s.hd, at, max_rows, st)) != LSV_OK) return rc;

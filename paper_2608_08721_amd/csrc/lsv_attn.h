@@ -1,11 +1,10 @@
 // Internal interface of the attention kernels (attention.hip).
 #pragma once
+#include "lsv_attn_plan.h"
 #include "lsv_device.h"
 #include "lsv_internal.h"
 
 namespace lsv {
-
-constexpr int kAttnChunk = 64;  // keys per LDS chunk in the bf16 split-context kernel
 
 // Column of cached position p in a transposed V row: positions are permuted inside each
 // aligned block of 32 so that the eight keys one lane feeds to a 16x16x32 MFMA (keys
@@ -56,24 +55,14 @@ struct AttnArgs {
   float* ml_part;  // [n_splits][M_max][nq][2]: running max (log2 units), sum of exponentials
   void* out;       // nq*hd columns per row in the activation layout (act_index), storage type
   float scale_log2;
-  int n_splits, chunks_per_split;
-  // packed grid (a 1-D grid of n_splits * nkv * batch workgroups): workgroup i takes the i-th
-  // (sequence, kv head, split) that holds keys instead of blockIdx = (split, kv head, sequence)
-  int packed;
-  // query groups: group g of a sequence's workgroups takes passes g, g + q_groups, ... over its tiles
-  int q_groups;
+  // packed plans (a 1-D grid): workgroup i takes the i-th (sequence, query group, kv head, split) that
+  // holds keys instead of blockIdx = (split, kv head, sequence)
+  AttnPlan plan;
   // tree blocks: [M_max][kAncWords] ancestor-or-self masks; a block key (position >= the
   // cached length C) at slot C + j is visible to row m iff bit j of its mask is set.  NULL:
   // the causal block.
   const uint32_t* anc;
 };
-
-// Split of the context into n_splits ranges of chunks_per_split chunks (bf16 path); packed:
-// the split kernel runs on a packed grid (AttnArgs::packed).
-struct AttnPlan {
-  int n_splits, chunks_per_split, packed, q_groups;
-};
-AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int max_ctx);
 
 int launch_attention(int dtype, int hd, const AttnArgs& a, int max_rows, hipStream_t st);
 

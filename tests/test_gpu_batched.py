@@ -96,6 +96,16 @@ def test_batched_body_rows_below_the_bound():
     _bf16_case(configs.SMALL_BF16, 28, [40], [70], bound=512)
 
 
+@pytest.mark.parametrize("contexts,rows", [([2500, 90], [4, 440]), ([60, 3000, 700], [100, 3, 300]),
+                                           ([1500], [65]), ([40, 40, 40, 40], [128] * 4)])
+def test_query_groups_beside_short_sequences(contexts, rows):
+    """A bound of 512 rows leaves room for query groups; each sequence takes them, or the context
+    splits of a short block, by its own rows: a decoding sequence beside a prefill chunk, one of few
+    query tiles between two of many, a block of 65 rows, and four alike."""
+    shape = dataclasses.replace(configs.SMALL_BF16, n_q_heads=32, n_kv_heads=8, n_layers=1, name="small-bf16-32-8")
+    _bf16_case(shape, 30, contexts, rows, bound=lsv.LSV_MAX_ROWS)
+
+
 def test_query_groups_lose_no_precision():
     """512 rows of one sequence behind 2,100 positions as one block, whose query tiles the attention
     takes in groups over one or two long splits, and as eight blocks of 64 rows over fourteen short

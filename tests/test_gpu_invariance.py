@@ -12,7 +12,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from paper_2608_08721_amd import runtime
+from paper_2608_08721_amd import lsv, runtime
 from synth import configs, gen
 from tests.lsv_testing import GpuModel, note
 
@@ -87,6 +87,32 @@ def test_row_logits_do_not_depend_on_the_body_of_33_to_64_rows():
             lg, st = gm.verify([C + pos], toks[pos:pos + n], [0, n], max_rows=132)
             assert st[0] == 0
             assert np.array_equal(lg, whole[pos:pos + n]), (sizes, pos)
+            pos += n
+
+
+@pytest.mark.parametrize("n_q_heads", [32, 64])
+def test_row_logits_do_not_depend_on_the_row_bound(n_q_heads):
+    """Behind 2,000 positions (33 chunks of keys, so that split plans can differ: 11 splits of 3) the
+    same 64 rows under row bounds of 64, 65, 132 and 512 -- the larger ones leave room for query
+    groups -- and as blocks of 9, 39 and 16 under 512 must give bit-identical logits, in groups of
+    four and eight query heads."""
+    shape = dataclasses.replace(configs.SMALL_BF16, n_q_heads=n_q_heads, n_kv_heads=8, n_layers=1,
+                                name=f"small-bf16-{n_q_heads}-8")
+    seed, C, R = 65, 2000, 64
+    w = gen.model_weights(shape, seed)
+    cap = runtime.kv_capacity(C + R + 8)
+    gm = GpuModel(shape, w, 1, cap, max_rows=lsv.LSV_MAX_ROWS)
+    k, v = gen.synthetic_kv(shape, seed, 0, 1, C)
+    gm.kv.write(0, 0, 0, runtime.to_device(k[0]), runtime.to_device(v[0]))
+    toks = gen.randint(seed, 900, R, shape.vocab)
+    whole, st = gm.verify([C], toks, [0, R], max_rows=64)
+    assert st[0] == 0 and np.isfinite(whole).all()
+    for sizes, bound in (([R], 65), ([R], 132), ([R], 512), ([9, 39, 16], 512)):
+        pos = 0
+        for n in sizes:
+            lg, st = gm.verify([C + pos], toks[pos:pos + n], [0, n], max_rows=bound)
+            assert st[0] == 0
+            assert np.array_equal(lg, whole[pos:pos + n]), (sizes, bound, pos)
             pos += n
 
 
