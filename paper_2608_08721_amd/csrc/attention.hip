@@ -326,12 +326,14 @@ __global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_ke
 #pragma unroll
           for (int ks = 0; ks < 2; ++ks) t[dt] = mfma_pv(g, dt, ks, pb[ks], t[dt]);
         }
-        if (!__all(alpha == 1.f)) {  // few chunks of a long split raise a row's maximum
+        const f32x4_t scale = {beta, beta, beta, beta};
+        if (__all(alpha == 1.f)) {  // most chunks of a long split raise no row's maximum
 #pragma unroll
-          for (int dt = 0; dt < HD / 16; ++dt) o[dt] *= alpha;
+          for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_elementwise_fma(t[dt], scale, o[dt]);
+        } else {
+#pragma unroll
+          for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_elementwise_fma(t[dt], scale, o[dt] * alpha);
         }
-#pragma unroll
-        for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_elementwise_fma(t[dt], f32x4_t{beta, beta, beta, beta}, o[dt]);
         return;
       }
       lrun = lrun * alpha + sum;
