@@ -96,3 +96,24 @@ def test_grid_and_partials_hold_every_block_under_the_bound(lib):
                         if packed:
                             assert units <= n_wgs, (nkv, group, batch, ctx, bound, rows)
     assert grouped > 500
+
+
+def test_query_groups_walk_hardly_longer_than_passes_would(lib):
+    """What a compute unit walks: chunks per split times the rounds of the grid (256 units), against the
+    same rows in passes over the context splits.  A group's loads serve one pass, so some more chunks
+    cost no more time, but few long splits of groups that leave most of the chip idle (17 groups of
+    eight kv heads) would walk up to 1.8 times as far."""
+    for nkv, group in HEADS:
+        for batch in (1, 2, 3, 4, 8):
+            for ctx in CONTEXTS:
+                for bound in (65, 97, 132, 200, 264, 320, 385, 512):
+                    rows = bound // batch
+                    if rows > ctx:
+                        continue
+                    n_splits, per_split = plan(lib, batch, nkv, group, bound, ctx)[:2]
+                    s, chunks, groups = sequence(lib, batch, nkv, group, bound, ctx, rows, ctx - rows, rows * batch)
+                    if groups == 1:
+                        continue
+                    passes = -(-rows * group // 128)
+                    walk = -(-batch * nkv * groups * s // 256) * chunks
+                    assert walk <= 1.4 * passes * per_split * -(-n_splits * nkv * batch // 256), (nkv, group, batch, ctx, bound)
