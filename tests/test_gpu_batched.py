@@ -1,5 +1,5 @@
 """GPU verify at the batched shapes: more than 64 block rows, which take the GEMMs' batched body
-and the attention's passes of query tiles.
+and the attention's passes and groups of query tiles.
 
 * small bf16 model (d 1024, 8/2 x 128 heads), 8 sequences x 33 rows = 264 rows over
   ragged contexts;
@@ -75,9 +75,9 @@ def test_llama70b_width_greedy_and_sampling():
 
 
 def test_short_blocks_under_a_batched_bound():
-    """Blocks of at most 64 rows under a bound above 64 (the selected lengths of a batch whose
-    worst case is large): the 64-row GEMM kernel serves them and the batched kernels, launched
-    too, return at once; Llama-3-70B width with 28 rows under a 132-row bound, the small model
+    """Blocks of at most 32 rows under a bound above 64 (the selected lengths of a batch whose
+    worst case is large): the one GEMM launch runs the 64-row bodies on them, and the split-K reduces,
+    launched too, return at once; Llama-3-70B width with 28 rows under a 132-row bound, the small model
     with 20 rows under 272."""
     _bf16_case(configs.LLAMA3_70B.with_layers(1), 24, [8192, 8100, 5000, 7000], [8, 8, 6, 6], bound=132)
     _bf16_case(configs.SMALL_BF16, 25, [300, 40, 129], [9, 5, 6], bound=272)
@@ -85,9 +85,21 @@ def test_short_blocks_under_a_batched_bound():
 
 @pytest.mark.parametrize("rows", [65, 128, 129, 257, 320, 321, 512])
 def test_batched_body_row_counts(rows):
-    """Row counts around the batched body's tilings (one to eight activation tiles per wave, one
-    chunk or two) on the tiny model, whose SwiGLU width of 688 ends in a k-block of six fragments."""
+    """Row counts around the batched body's tilings (two to five activation tiles per wave: few column
+    tiles take two chunks above 320 rows) on the tiny model, whose SwiGLU width of 688 ends in a k-block
+    of six fragments."""
     _bf16_case(configs.TINY_BF16, 26, [40, 7], [rows - 20, 20])
+
+
+@pytest.mark.parametrize("rows", [336, 384, 385, 448, 449, 512])
+@pytest.mark.parametrize("d_model", [320, 576])
+def test_batched_body_many_activation_tiles(rows, d_model):
+    """Six to eight activation tiles per wave: gate/up and the LM head of 65 column tiles keep more than
+    320 rows in one chunk.  d_model 320 gives one k range of ten steps, 576 two of nine, which is an odd
+    step before the loop; both end in a k-block of two fragments."""
+    shape = dataclasses.replace(configs.TINY_BF16, d_model=d_model, d_ff=4112, vocab=8320, n_layers=1,
+                                name=f"tiny-bf16-65-tiles-{d_model}")
+    _bf16_case(shape, 31, [40, 7], [rows - 20, 20])
 
 
 def test_batched_body_rows_below_the_bound():
