@@ -158,8 +158,11 @@ size_t lsv_kv_pool_bytes(const lsv_model_config* cfg, int32_t n_pages);
 /* Workspace for lsv_verify_block with the given bounds.  The workspace must be
  * zero-filled once after allocation (e.g. with lsv_workspace_clear): the padding
  * columns of its activation buffers are never written and must read as zero.  It
- * carries no state from one call to the next, and a workspace sized for the largest
- * bounds serves calls with any smaller batch, max_rows or max_ctx. */
+ * carries no state from one call to the next, and serves calls with the same batch and
+ * max_ctx and any smaller max_rows.  A smaller batch or max_ctx can take more context
+ * splits, whose partials need more space (one sequence, 8 kv heads: 11 splits under a
+ * bound of 2,112 positions, 16 under 2,048): a program whose bounds change takes the largest of
+ * their sizes.  A call whose workspace is too small gets LSV_ERR_INVALID_ARG. */
 size_t lsv_verify_workspace_bytes(const lsv_model_config* cfg, int32_t batch, int32_t max_rows,
                                   int32_t max_ctx);
 int lsv_workspace_clear(void* d_workspace, size_t workspace_bytes, void* stream);

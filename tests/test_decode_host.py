@@ -1,5 +1,7 @@
 """Host-side checks of the decoding loop driver (no GPU): bad policies and missing cost
 tables are refused before any device buffer is made."""
+import dataclasses
+
 import pytest
 
 from paper_2608_08721_amd import decode
@@ -22,6 +24,23 @@ def test_cost_table_too_short(policy, n):
     refused (B = 2, G = 4 here)."""
     with pytest.raises(ValueError, match="cost entries"):
         decode.DecodeLoop(None, None, None, 128, 2, 4, policy, None, cost=[1.0] * n)
+
+
+@pytest.mark.parametrize("capacity,max_ctx", [(2112, 2048), (2112, None), (8256, 8192), (8192, 700)])
+def test_workspace_fits_the_context_bound_of_the_calls(monkeypatch, capacity, max_ctx):
+    """A smaller context bound can take more attention splits (16 under 2,048 positions, 11 under
+    2,112): the loop's workspace must hold what its verify calls, made with max_ctx, ask for."""
+    from paper_2608_08721_amd import lsv, runtime
+    from synth import configs
+
+    class HostWorkspace:
+        def __init__(self, nbytes):
+            self.nbytes, self.buf = nbytes, None
+
+    monkeypatch.setattr(runtime, "Workspace", HostWorkspace)
+    cfg = runtime.model_config(dataclasses.replace(configs.SMALL_BF16, n_kv_heads=8))
+    loop = decode.DecodeLoop(cfg, None, None, capacity, 1, 16, "alg1", None, max_ctx=max_ctx, device="cpu")
+    assert loop.ws.nbytes >= lsv.lsv_verify_workspace_bytes(cfg, 1, loop.max_rows, loop.max_ctx)
 
 
 def test_binding_checks_selector_tables():
