@@ -85,11 +85,13 @@ LSV_DEV bool packed_unit(const AttnArgs& a, int i, SplitUnit& u) {
   return true;
 }
 
-// Registers are held to two waves per SIMD at head dimension 128 and four at 64: left to itself the
-// compiler takes 276 and 160 in the four-wave kernel (Llama-3-8B, 32 paged sequences: 1502 -> 1549 us).
+// Registers are held to two waves per SIMD: left to itself the compiler takes 276 in the four-wave kernel
+// at head dimension 128 (Llama-3-8B, 32 paged sequences: 1502 -> 1549 us).  Head dimension 64 stays far
+// below that (holding it to four waves per SIMD spilled: 32 heads over 8, batch 4, 2 rows behind 4,000
+// positions, four layers: 275 -> 279 us).
 // Plans with query groups (GROUPED) have eight waves: more than kGroupTiles query tiles.
 template <int HD, int NW, bool GROUPED = false>
-__global__ void __launch_bounds__(64 * NW, HD == 128 ? 2 : 4) attn_split_bf16_kernel(AttnArgs a) {
+__global__ void __launch_bounds__(64 * NW, 2) attn_split_bf16_kernel(AttnArgs a) {
   constexpr int NG = NW / 4;               // wave groups: each loads one chunk per step
   constexpr int P8 = HD / 8;               // 16-byte pieces per K row
   constexpr int NP = kCh * HD / 8 / 256;   // pieces of K (and of V^T) per thread of a group and chunk
