@@ -197,9 +197,9 @@ int lsv_workspace_clear(void* d_workspace, size_t workspace_bytes, void* stream)
  *   d_workspace        lsv_verify_workspace_bytes(cfg, batch, max_rows, max_ctx) bytes */
 enum { LSV_MAX_BATCH = 64, LSV_MAX_ROWS = 512 };
 /* Performance note: bf16 blocks of more than 64 rows (under a host bound above 64) run the
- * batched GEMM path: weights and activations through LDS, matrix-core bound.  fp32 models
- * process rows in chunks of 64.  LSV_WIDE_ROWS: a bound that keeps every row of a block in one
- * workgroup per column tile. */
+ * batched GEMM path: weights and activations through LDS, matrix-core bound; products that do not
+ * split K do so from 33 rows on.  fp32 models process rows in chunks of 64.  Up to LSV_WIDE_ROWS rows,
+ * every product keeps the rows of a column tile in one workgroup (above, some split them in two). */
 enum { LSV_WIDE_ROWS = 272 };
 int lsv_verify_block(const lsv_model_config* cfg, const void* d_packed, void* d_kv, int32_t capacity,
                      int32_t batch, const int32_t* d_seq_len, const int32_t* d_tokens,

@@ -430,8 +430,6 @@ int launch_verify(const Shape& s, const ModelLayout& ml, const void* packed, voi
   };
 
   GemmArgs base = {};
-  base.rows_lo = -1;
-  base.rows_hi = kRowsAny;
   base.M_max = max_rows;
   base.batch = batch;
   base.row_offsets = row_offsets;

@@ -517,7 +517,6 @@ __global__ void __launch_bounds__(64 * GemmCfg<KIND>::KS) gemm_kernel(GemmArgs a
   const int round = blockIdx.x >> 3, chunk = round % nch, tile = (round / nch) * 8 + (blockIdx.x & 7);
   if (tile >= tiles) return;
   const int rows = GL(a.row_offsets)[a.batch];
-  if (rows <= a.rows_lo || rows > a.rows_hi) return;  // another launch serves this row count
   const int M = min(rows, a.M_max);  // never trust device rows beyond the host bound
   const int m0 = chunk * 64;
   if (m0 >= M) return;
@@ -773,13 +772,17 @@ LSV_DEV void gemm_tile_body(const GemmArgs& a, const int M, const int tile, cons
   gemm_epilogue<T, MTW, FRW, EPI, false>(a, M_end, m0, tn0, tvalid, acc, none);
 }
 
-// One launch for blocks under a batched row bound (64 < bound <= kWideRows).  Up to 64 device
-// rows, each of a workgroup's four waves runs the 64-row body on a column tile of its own --
+// One launch for blocks under a batched row bound (65 .. LSV_MAX_ROWS).  Up to 64 device
+// rows (32 where one k range lets gate/up and the LM head take either body), each of a workgroup's
+// four waves runs the 64-row body on a column tile of its own --
 // tile (wave x grid + workgroup), so that the busy waves spread over the compute units -- and
 // streams its weights once, as gemm_kernel does (gate/up of the wider models with up to 32 rows
 // takes its eight-fragment-row configuration); more rows run the batched body on the
 // workgroup's (tile, k range, row chunk).  One launch instead of one of each kind, one of
-// which would find no work.
+// which would find no work.  All bodies share the registers and LDS of the widest one (512 with 12 to
+// 20 spilled outside the k loops, 160 KiB: one wave per SIMD); the 64-row bodies ran at one wave per
+// SIMD before that too, and lost nothing (4 to 32 rows under a bound of 132, one or two layers of
+// Llama-3-8B, Qwen2.5-32B and Llama-3-70B: 1.01 to 1.03 times as fast as with 480 registers and 16 KiB).
 template <int KIND, int WIDE_EPI>
 __global__ void __launch_bounds__(64 * kTileWaves) gemm_fused_kernel(GemmArgs a) {
   __shared__ u32x4_t lds[kTileLds];
@@ -787,7 +790,9 @@ __global__ void __launch_bounds__(64 * kTileWaves) gemm_fused_kernel(GemmArgs a)
   // A product in one k range adds its k-steps in the same order in both bodies, so its rows' bits do
   // not depend on which one ran: gate/up and the LM head take the batched one from 33 rows on, whose
   // shared operands move fewer bytes per row tile (Qwen2.5-32B, 38 rows: gate/up 104 -> 97 us, LM head
-  // 287 -> 269).
+  // 287 -> 269; whole calls of 33 to 64 rows at Llama-3-8B, Qwen2.5-32B and Llama-3-70B width 5 to 11%
+  // faster).  17 to 32 rows are mixed: Llama-3-8B 251 -> 252 and 254 -> 257 us (24 and 32 rows, two
+  // layers), Qwen2.5-32B 260 -> 255 and 266 -> 261, Llama-3-70B 370 -> 366 and 373 -> 368 (one layer).
   constexpr bool kEither = KIND == GEMM_GATEUP || KIND == GEMM_LMHEAD;
   if (M <= 64 && !(kEither && M > 32 && a.splits == 1 && a.chunks == 1)) {
     if (M <= 0) return;
@@ -877,7 +882,7 @@ __global__ void __launch_bounds__(256) gemm_wide_reduce_kernel(GemmArgs a) {
   const int tile = blockIdx.x, m0 = blockIdx.y * 16, S = a.splits;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
   const int rows = GL(a.row_offsets)[a.batch];
-  if (rows <= a.rows_lo || rows > a.rows_hi) return;
+  if (rows <= 64) return;  // the 64-row bodies finished the product
   const int M = min(rows, a.M_max);
   if (m0 >= M) return;
   const int tn0 = (tile * 4 + wave) * TPW, m = m0 + l16;
@@ -915,7 +920,7 @@ __global__ void __launch_bounds__(256) gemm_wide_reduce_kernel(GemmArgs a) {
 // four columns per thread.
 __global__ void __launch_bounds__(256) qkv_rope_kernel(GemmArgs a, const float* y) {
   const int rows = GL(a.row_offsets)[a.batch];
-  if (rows <= a.rows_lo || rows > a.rows_hi) return;
+  if (rows <= 64) return;  // the 64-row bodies finished the product
   const int M = min(rows, a.M_max);
   const int groups = a.N / 4;
   const size_t n = (size_t)M * groups;
@@ -938,7 +943,10 @@ WidePlan plan_wide(int Nt, int Kt, int max_rows) {
   // workgroup.  Every row in one workgroup reads the weights once, but a product of few tiles would
   // then take more k ranges, whose partials grow with rows x ranges: two row chunks halve them.
   // Llama-3-8B width, 512 rows: gate/up (224 tiles) stays in one chunk; QKV (48), O and down (32)
-  // take two.
+  // take two.  One chunk against two at kWideOneChunk rows and below, one layer and a small head:
+  // Llama-3-70B 457 / 491 us (132 rows), 531 / 555 (200), 645 / 662 (264), 701 / 699 (320);
+  // Qwen2.5-32B 303 / 327, 355 / 367, 426 / 429, 456 / 453; Llama-3-8B 201 / 209, 227 / 229, 266 / 258,
+  // 287 / 272, which alone would gain from a lower line.
   p.chunks = max_rows > kWideOneChunk && p.tiles <= kComputeUnits / 4 ? 2 : 1;
   p.splits = kComputeUnits / (p.tiles * p.chunks);
   const int most = Kt / 8;
@@ -966,21 +974,18 @@ int launch_gemm_fused(GemmKind kind, const GemmArgs& a0, const WidePlan& p, hipS
   GemmArgs a = a0;
   a.splits = p.splits;
   a.chunks = p.chunks;
-  GemmArgs big = a;  // the passes after the batched body: only for more than 64 rows
-  big.rows_lo = 64;
   const dim3 rgrid((unsigned)p.tiles, (unsigned)((a.M_max + 15) / 16));
   switch (kind) {
     case GEMM_QKV:
       if (p.splits > 1) {
         launch_fused_one<GEMM_QKV, EPI_LOGITS>(a, p, st);
-        hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_QKV>, rgrid, dim3(256), 0, st, big);
+        hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_QKV>, rgrid, dim3(256), 0, st, a);
       } else {
         if (!a.out_f32) return LSV_ERR_INVALID_ARG;
         a.ldo = a.N;  // the batched body writes the projection to out_f32; the 64-row body does not read it
-        big.ldo = a.N;
         launch_fused_one<GEMM_QKV, EPI_LOGITS>(a, p, st);
         const size_t n = (size_t)a.M_max * (a.N / 4);
-        hipLaunchKernelGGL(qkv_rope_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, big, big.out_f32);
+        hipLaunchKernelGGL(qkv_rope_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a, a.out_f32);
       }
       break;
     case GEMM_O:  // k-split partials are added by the next row normalisation
@@ -988,14 +993,14 @@ int launch_gemm_fused(GemmKind kind, const GemmArgs& a0, const WidePlan& p, hipS
       break;
     case GEMM_GATEUP:
       launch_fused_one<GEMM_GATEUP, EPI_SWIGLU>(a, p, st);
-      if (p.splits > 1) hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_SWIGLU>, rgrid, dim3(256), 0, st, big);
+      if (p.splits > 1) hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_SWIGLU>, rgrid, dim3(256), 0, st, a);
       break;
     case GEMM_DOWN:  // k-split partials are added by the next row normalisation
       launch_fused_one<GEMM_DOWN, EPI_RESID>(a, p, st);
       break;
     case GEMM_LMHEAD:
       launch_fused_one<GEMM_LMHEAD, EPI_LOGITS>(a, p, st);
-      if (p.splits > 1) hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_LOGITS>, rgrid, dim3(256), 0, st, big);
+      if (p.splits > 1) hipLaunchKernelGGL(gemm_wide_reduce_kernel<EPI_LOGITS>, rgrid, dim3(256), 0, st, a);
       break;
   }
   return hipGetLastError() == hipSuccess ? LSV_OK : LSV_ERR_HIP;

@@ -22,7 +22,13 @@ constexpr int kAttnChunk = 64;  // keys per LDS chunk in the bf16 split-context 
 constexpr int kAttnWgs = 128;
 constexpr int kMaxChunksPerSplit = 16;
 constexpr int kAttnUnits = 256;  // compute units of gfx950 (MI350X, MI355X)
-// Query groups: for sequences of more than kGroupTiles query tiles in a block of more than kGroupRows rows
+// Query groups: for sequences of more than kGroupTiles query tiles in a block of more than kGroupRows
+// rows.  Above the line, passes against groups, two layers at Llama-3-8B width: 97 rows (25 tiles) behind
+// 500 / 2,000 / 8,000 positions 361 / 386 / 439 us against 339 / 347 / 383, 128 rows 382 / 410 / 470
+// against 353 / 365 / 405; one layer at Llama-3-70B width, 4 x 49 rows behind 8,000: 640 against 618.
+// Below it, one sequence would gain as well (96 rows: 349 / 367 / 413 against 333 / 342 / 371), four of
+// 33 rows at Llama-3-70B width would lose behind 8,000 positions (534 against 541) and gain behind 500
+// (468 against 449).
 constexpr int kGroupRows = 64;
 constexpr int kGroupTiles = 24;
 constexpr int kPassTiles = 8;  // query tiles of one pass (a group): one for each of the eight waves

@@ -43,9 +43,6 @@ LSV_DEV __amdgpu_buffer_rsrc_t stream_rsrc(const void* p, size_t bytes) {
 LSV_DEV u32x4_t load_stream(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kBufferStream));
 }
-// The same through a global address (the batched GEMM body, where buffer loads lost 0.3%).
-template <typename T> LSV_DEV T load_stream(const GLOBAL T* p) { return __builtin_nontemporal_load(p); }
-
 // 64 lanes x 16 bytes straight into LDS: lane l's piece goes to dst[l] (dst wave-uniform) from byte
 // voff + soff (soff wave-uniform).  The load counts as one outstanding vector-memory operation.
 template <int AUX> LSV_DEV void load_lds(__amdgpu_buffer_rsrc_t r, u32x4_t* dst, uint32_t voff, uint32_t soff) {

@@ -46,12 +46,7 @@ struct GemmArgs {
   void* u_out;  // SwiGLU output, F columns (act_index)
   int F;
   int layer_index;  // host-side only: which layer a launch belongs to (measurement hook)
-  // device row range a launch serves: it does nothing unless rows_lo < rows <= rows_hi,
-  // rows = row_offsets[batch] (blocks under a batched bound launch both the 64-row kernel
-  // and the batched one, and the device row count picks which of them works)
-  int rows_lo, rows_hi;
 };
-constexpr int kRowsAny = 0x7fffffff;
 
 // One launch: a workgroup per tile of output columns, the whole K per workgroup.
 int launch_gemm(int dtype, GemmKind kind, int MT, const GemmArgs& a, hipStream_t st);
