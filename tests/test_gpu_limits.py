@@ -1,8 +1,8 @@
 """The C-ABI's maximum sizes on the GPU, against the oracle:
 
 * lsv_verify_block with LSV_MAX_ROWS = 512 block rows: 64 sequences (LSV_MAX_BATCH) of 8 rows
-  over ragged contexts, one sequence of 512 rows (128 query tiles of a 4-head group: sixteen
-  passes of the eight-wave attention split kernel), and the fp32 model at 512 rows (bar 1e-5);
+  over ragged contexts, one sequence of 512 rows (128 query tiles of a 4-head group: sixteen query groups of one
+  pass of the eight-wave attention split kernel each), and the fp32 model at 512 rows (bar 1e-5);
   bf16 bounds of 512 rows take the batched GEMM body, fp32 ones the 64-row-chunk GEMMs (eight
   chunks);
 * lsv_accept, greedy and sampling, with 512 rows as 64 sequences of 8 and as 8 sequences of
