@@ -82,7 +82,9 @@ class DecodeLoop:
             self.draft_probs = torch.zeros((B * max(G, 1) + 1, cfg.vocab), dtype=torch.float32, device=device)
             self.kk = torch.arange(max(G, 1), dtype=torch.int64, device=device)
             self.bb = torch.arange(B, dtype=torch.int64, device=device)
-        self.ws = runtime.Workspace(lsv.lsv_verify_workspace_bytes(cfg, B, self.max_rows, self.max_ctx))
+        # a smaller context bound can take more attention splits, and so a larger workspace
+        self.ws = runtime.Workspace(max(lsv.lsv_verify_workspace_bytes(cfg, B, self.max_rows, c)
+                                        for c in (self.max_ctx, capacity)))
         self.aws = runtime.Workspace(lsv.lsv_accept_workspace_bytes(B, self.max_rows, cfg.vocab))
         g0 = G if gamma0 is None else gamma0
         self.gamma0 = g0

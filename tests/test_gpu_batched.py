@@ -15,11 +15,12 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import accept as OA
-from paper_2608_08721_amd import lsv
+from paper_2608_08721_amd import lsv, runtime
 from synth import configs, gen
-from tests.lsv_testing import note
+from tests.lsv_testing import GpuModel, i32, note
 from tests.test_gpu_accept import gpu_accept, unsettled
 from tests.test_gpu_forward import _bf16_case
 
@@ -137,3 +138,36 @@ def test_query_groups_lose_no_precision():
     e_whole, e_short = np.linalg.norm(whole - want) / scale, np.linalg.norm(np.concatenate(short) - want) / scale
     note(f"  512 rows off float64: {e_whole:.3e} as one block, {e_short:.3e} as blocks of 64 ({e_whole / e_short:.4f})")
     assert e_whole <= 1.005 * e_short
+
+
+def test_one_capture_serves_short_blocks_and_query_groups():
+    """A verify call captured once under a bound of 512 rows finds its plan from the device rows of each
+    replay: one of query groups, one of context splits, mixed batches, and again."""
+    shape = dataclasses.replace(configs.SMALL_BF16, n_q_heads=32, n_kv_heads=8, n_layers=1, name="small-bf16-32-8")
+    seed, C, B, R = 32, [700, 300], 2, lsv.LSV_MAX_ROWS
+    cap = runtime.kv_capacity(max(C) + R)
+    gm = GpuModel(shape, gen.model_weights(shape, seed), B, cap, max_rows=R)
+    for b in range(B):
+        k, v = gen.synthetic_kv(shape, seed + b, 0, 1, C[b])
+        gm.kv.write(0, b, 0, runtime.to_device(k[0]), runtime.to_device(v[0]))
+    toks, seq_len, off = i32(gen.randint(seed, 900, R, shape.vocab)), i32(C), i32([0, 0, 0])
+
+    def call():
+        lsv.lsv_verify_block(gm.cfg, gm.dm.buf, gm.kv.buf, cap, B, seq_len, toks, off, R, cap, gm.logits, gm.status,
+                             gm.ws.buf, gm.ws.nbytes)
+
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for rows in ([256, 256], [9, 3], [500, 4], [3, 200], [256, 256], [9, 3]):
+        off.copy_(i32([0, rows[0], sum(rows)]))
+        call()
+        torch.cuda.synchronize()
+        want = gm.logits[:sum(rows)].clone()
+        gm.logits.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(gm.logits[:sum(rows)], want) and bool(torch.isfinite(want).all()), rows
+        assert not gm.status.any()
