@@ -772,6 +772,15 @@ LSV_DEV void gemm_tile_body(const GemmArgs& a, const int M, const int tile, cons
   gemm_epilogue<T, MTW, FRW, EPI, false>(a, M_end, m0, tn0, tvalid, acc, none);
 }
 
+// The body for mtw <= MTW activation tiles per wave.
+template <int EPI, int MTW>
+LSV_DEV void gemm_tile_pick(int mtw, const GemmArgs& a, const int M, const int tile, const int j, const int mt_base,
+                            const int mt_end, u32x4_t* lds) {
+  if constexpr (MTW > 1)
+    if (mtw < MTW) return gemm_tile_pick<EPI, MTW - 1>(mtw, a, M, tile, j, mt_base, mt_end, lds);
+  gemm_tile_body<EPI, MTW>(a, M, tile, j, mt_base, mt_end, lds);
+}
+
 // One launch for blocks under a batched row bound (65 .. LSV_MAX_ROWS).  Up to 64 device
 // rows (32 where one k range lets gate/up and the LM head take either body), each of a workgroup's
 // four waves runs the 64-row body on a column tile of its own --
@@ -779,11 +788,13 @@ LSV_DEV void gemm_tile_body(const GemmArgs& a, const int M, const int tile, cons
 // streams its weights once, as gemm_kernel does (gate/up of the wider models with up to 32 rows
 // takes its eight-fragment-row configuration); more rows run the batched body on the
 // workgroup's (tile, k range, row chunk).  One launch instead of one of each kind, one of
-// which would find no work.  All bodies share the registers and LDS of the widest one (512 with 12 to
-// 20 spilled outside the k loops, 160 KiB: one wave per SIMD); the 64-row bodies ran at one wave per
-// SIMD before that too, and lost nothing (4 to 32 rows under a bound of 132, one or two layers of
-// Llama-3-8B, Qwen2.5-32B and Llama-3-70B: 1.01 to 1.03 times as fast as with 480 registers and 16 KiB).
-template <int KIND, int WIDE_EPI>
+// which would find no work.  All bodies share the registers and LDS of the widest one (up to 480, and
+// 160 KiB: one wave per SIMD); the 64-row bodies ran at one wave per SIMD before that too.
+// MTW_MAX: the most activation tiles per wave that the row bound can need.  Eight spill 12 to 20
+// registers outside the k loop, so only bounds that need eight (above 448 rows in one chunk) launch them:
+// a user of scratch memory among the launches slows the small kernels behind it (Llama-3-70B, 16 rows
+// under a bound of 132: attention merge 4.8 -> 5.3 us, normalisation 4.8 -> 5.3, QKV 30.7 -> 31.9).
+template <int KIND, int WIDE_EPI, int MTW_MAX>
 __global__ void __launch_bounds__(64 * kTileWaves) gemm_fused_kernel(GemmArgs a) {
   __shared__ u32x4_t lds[kTileLds];
   const int M = min(GL(a.row_offsets)[a.batch], a.M_max);  // never trust device rows beyond the host bound
@@ -862,16 +873,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) gemm_fused_kernel(GemmArgs a)
   const int mt0 = round % a.chunks * per, mt1 = min(mt0 + per, mt_all);
   if (mt0 >= mt1) return;
   const int tile = pair / a.splits, j = pair % a.splits;
-  switch ((per + kTileWaves - 1) / kTileWaves) {  // activation tiles per wave
-    case 1: return gemm_tile_body<WIDE_EPI, 1>(a, M, tile, j, mt0, mt1, lds);
-    case 2: return gemm_tile_body<WIDE_EPI, 2>(a, M, tile, j, mt0, mt1, lds);
-    case 3: return gemm_tile_body<WIDE_EPI, 3>(a, M, tile, j, mt0, mt1, lds);
-    case 4: return gemm_tile_body<WIDE_EPI, 4>(a, M, tile, j, mt0, mt1, lds);
-    case 5: return gemm_tile_body<WIDE_EPI, 5>(a, M, tile, j, mt0, mt1, lds);
-    case 6: return gemm_tile_body<WIDE_EPI, 6>(a, M, tile, j, mt0, mt1, lds);
-    case 7: return gemm_tile_body<WIDE_EPI, 7>(a, M, tile, j, mt0, mt1, lds);
-    default: return gemm_tile_body<WIDE_EPI, 8>(a, M, tile, j, mt0, mt1, lds);  // LSV_MAX_ROWS in one chunk
-  }
+  gemm_tile_pick<WIDE_EPI, MTW_MAX>((per + kTileWaves - 1) / kTileWaves, a, M, tile, j, mt0, mt1, lds);
 }
 
 // Split-K sums of the batched GEMM: one workgroup per (tile, 16 rows) adds the k ranges in
@@ -967,7 +969,14 @@ static void launch_fused_one(const GemmArgs& a, const WidePlan& p, hipStream_t s
   const int skinny_wgs = ((a.Nt + S::TPW - 1) / S::TPW + 3) / 4;
   const int wide_wgs = p.chunks == 1 ? p.tiles * p.splits : (p.tiles * p.splits + 7) / 8 * 8 * p.chunks;
   const int grid = wide_wgs > skinny_wgs ? wide_wgs : skinny_wgs;
-  hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI>), dim3((unsigned)grid), dim3(64 * kTileWaves), 0, st, a);
+  const int mtw = (((a.M_max + 15) / 16 + p.chunks - 1) / p.chunks + kTileWaves - 1) / kTileWaves;  // at the bound
+  const dim3 g((unsigned)grid), block(64 * kTileWaves);
+  if constexpr (KIND == GEMM_O || KIND == GEMM_DOWN)  // at most 64 column tiles (d_model <= 8192): two chunks above 320 rows
+    hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI, 5>), g, block, 0, st, a);
+  else if (mtw <= 7)
+    hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI, 7>), g, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((gemm_fused_kernel<KIND, WIDE_EPI, 8>), g, block, 0, st, a);
 }
 
 int launch_gemm_fused(GemmKind kind, const GemmArgs& a0, const WidePlan& p, hipStream_t st) {
