@@ -31,13 +31,13 @@ template <bool GROUPED>
 LSV_DEV SeqPlan plan_of(const AttnArgs& a, int r0, int r1, int C, int M) {
   const int rows = r0 < 0 || r1 > a.M_max ? 0 : r1 - r0;
   if (GROUPED) return seq_plan(a.plan, a.batch, a.nkv, a.ctx_limit, rows, C, M);
-  return SeqPlan{splits_with_keys(a.plan.chunks_per_split, a.ctx_limit, rows, C), a.plan.chunks_per_split, 1};
+  return SeqPlan{splits_with_keys(a.plan.chunks_per_split, a.ctx_limit, rows, C), a.plan.chunks_per_split, 1, 0};
 }
 
 // What a workgroup of the split kernel takes: split s of kv head kvh of sequence b, `chunks` chunks a
-// split, and group g of `groups` of its query tiles.
+// split, and group g of `groups` of its query tiles; coarse: SeqPlan's.
 struct SplitUnit {
-  int s, kvh, b, chunks, g, groups;
+  int s, kvh, b, chunks, g, groups, coarse;
 };
 
 // Packed grid: workgroup i takes the i-th split that holds keys -- every sequence's full splits
@@ -48,7 +48,7 @@ struct SplitUnit {
 template <bool GROUPED>
 LSV_DEV bool packed_unit(const AttnArgs& a, int i, SplitUnit& u) {
   const int lane = threadIdx.x & 63;
-  SeqPlan p{0, 1, 1};
+  SeqPlan p{0, 1, 1, 0};
   if (lane < a.batch)
     p = plan_of<GROUPED>(a, GL(a.row_offsets)[lane], GL(a.row_offsets)[lane + 1], GL(a.seq_len)[lane],
                          GL(a.row_offsets)[a.batch]);
@@ -78,6 +78,7 @@ LSV_DEV bool packed_unit(const AttnArgs& a, int i, SplitUnit& u) {
   }
   u.chunks = __builtin_amdgcn_readlane(p.chunks, bb);
   u.groups = __builtin_amdgcn_readlane(p.groups, bb);
+  u.coarse = __builtin_amdgcn_readlane(p.coarse, bb);
   u.kvh = local % a.nkv;
   const int t = local / a.nkv;
   u.g = in_full ? t / (splits - 1) : t;
@@ -102,7 +103,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_split_bf16_kernel(AttnArgs a)
   __shared__ __align__(16) bf16_t Ks[NG][kCh * KPITCH];  // one chunk buffer per group
   __shared__ __align__(16) bf16_t Vt[NG][HD * VPITCH];
 
-  SplitUnit unit{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, a.plan.chunks_per_split, 0, 1};
+  SplitUnit unit{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, a.plan.chunks_per_split, 0, 1, 0};
   if (a.plan.packed && !packed_unit<GROUPED>(a, blockIdx.x, unit)) return;
   const int s = unit.s, kvh = unit.kvh, b = unit.b;
   // left to run time: as constants they make the compiler peel the first pass, which was slower
@@ -186,7 +187,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_split_bf16_kernel(AttnArgs a)
   const int c1_all = min(c0 + unit.chunks, nch);
   const size_t prow = (size_t)s * a.M_max + r0;  // this split's partial row of the sequence's first row
   if (c0 >= c1_all) return;  // no key of this split exists for the sequence: the merge does not read it
-  const bool local = GROUPED && unit.groups > 1;  // chunk maxima (see consume)
+  const bool local = GROUPED && unit.coarse;  // chunk maxima (see consume)
   // A pass over the split covers up to NW query tiles, one per wave, each wave running its
   // tile over all chunks in order.  Every tile takes the same chunk order and the same
   // arithmetic whatever the block's tile count, so a row's result does not depend on how
@@ -227,7 +228,7 @@ __global__ void __launch_bounds__(64 * NW, 2) attn_split_bf16_kernel(AttnArgs a)
     // its scores are finite (exp2 needs no guard); only chunks that reach the block's own
     // keys apply the causal and length mask.  Both take the same hardware exp2, so a key
     // contributes the same bits whether or not its chunk was masked.
-    // local (query groups): the probabilities are rounded to bf16 relative to the chunk's own
+    // local (coarse splits): the probabilities are rounded to bf16 relative to the chunk's own
     // maximum, and their product with V joins the running one scaled in fp32.  The heaviest key of
     // every chunk is then exact; under the running maximum only those are that raise it, which is
     // few of them in a group's one or two long splits (Llama-3-8B width, one layer, a tree of 512

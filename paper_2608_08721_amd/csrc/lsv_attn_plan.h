@@ -71,6 +71,13 @@ LSV_PLAN int group_chunks(int n_chunks, int units, int groups, int n_splits) {
   return chunks;
 }
 
+// Query groups of a sequence in the plan's own splits (of which the batch has `wgs`): one per pass, as far
+// as the compute units have room.
+LSV_PLAN int short_groups(int wgs, int passes) {
+  const int room = kAttnUnits / wgs;
+  return room < 1 ? 1 : (room < passes ? room : passes);
+}
+
 // Long contexts over many (sequence, kv head) pairs -- when one round's splits would walk more
 // than twice the length cap -- take a whole number of rounds' worth of splits instead, on a
 // packed grid: the splits that hold keys come first, so in a batch of ragged contexts the
@@ -88,8 +95,10 @@ LSV_PLAN int group_chunks(int n_chunks, int units, int groups, int n_splits) {
 // kv heads.  The device row counts decide this, sequence by sequence (seq_plan): under a large row
 // bound a short block keeps the splits above, and with them its parallelism and its bits (Llama-3-8B,
 // 9 rows behind 8,000 positions, two layers under a bound of 264 rows: 294 us in the splits that the
-// bound's groups would leave, 235 in these, 229 under a bound of 64).  The row bound only decides
-// whether the grid has room for groups.
+// bound's groups would leave, 235 in these, 229 under a bound of 64).  As far as the compute units
+// have room, its passes get workgroups of their own over the same splits, with the same bits (64 rows
+// behind 8,000 positions under a bound of 264: 376 us in one workgroup per split, 347 in two; 431 in the
+// bound's).  The row bound only decides whether the grid has room for groups.
 inline AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int max_ctx) {
   const int n_chunks = (max_ctx + kAttnChunk - 1) / kAttnChunk;
   const int units = batch * nkv;
@@ -117,9 +126,13 @@ inline AttnPlan plan_attention(int batch, int nkv, int group, int max_rows, int 
     // at most max_rows times the largest gain(g) / r(g)
     p.packed = 1;
     int extra = 0, most = 0;
-    for (int g = kGroupTiles / kPassTiles + 1; (g - 1) * kPassTiles < query_tiles(max_rows, group); ++g) {
-      const int cps = group_chunks(n_chunks, units, g, p.n_splits);
-      const int gain = nkv * (g * ((n_chunks + cps - 1) / cps) - p.n_splits);
+    for (int g = 2; (g - 1) * kPassTiles < query_tiles(max_rows, group); ++g) {
+      int gain = nkv * p.n_splits * (short_groups(units * p.n_splits, g) - 1);
+      if (g * kPassTiles > kGroupTiles) {
+        const int cps = group_chunks(n_chunks, units, g, p.n_splits);
+        const int coarse = nkv * (g * ((n_chunks + cps - 1) / cps) - p.n_splits);
+        if (coarse > gain) gain = coarse;
+      }
       const int r = 16 * (g - 1) * kPassTiles / group + 1;  // (g - 1) * kPassTiles + 1 tiles or more
       if (gain > most) most = gain;
       if (max_rows * gain / r > extra) extra = max_rows * gain / r;
@@ -140,16 +153,19 @@ LSV_PLAN int splits_with_keys(int chunks, int ctx_limit, int rows, int C) {
 
 // How a sequence of `rows` rows behind C cached positions, in a block of M rows, is divided: `splits`
 // runs of `chunks` chunks that hold keys (at most AttnPlan::n_splits, since positions past ctx_limit
-// do not count) and `groups` of query tiles.
+// do not count) and `groups` of query tiles; coarse: in splits of its own, not the plan's.
 struct SeqPlan {
-  int splits, chunks, groups;
+  int splits, chunks, groups, coarse;
 };
 LSV_PLAN SeqPlan seq_plan(const AttnPlan& p, int batch, int nkv, int ctx_limit, int rows, int C, int M) {
-  SeqPlan q = {0, p.chunks_per_split, 1};
-  const int tiles = query_tiles(rows, p.group);
+  SeqPlan q = {0, p.chunks_per_split, 1, 0};
+  const int tiles = query_tiles(rows, p.group), passes = (tiles + kPassTiles - 1) / kPassTiles;
   if (p.grouped && M > kGroupRows && tiles > kGroupTiles) {
-    q.groups = (tiles + kPassTiles - 1) / kPassTiles;
-    q.chunks = group_chunks((ctx_limit + kAttnChunk - 1) / kAttnChunk, batch * nkv, q.groups, p.n_splits);
+    q.coarse = 1;
+    q.groups = passes;
+    q.chunks = group_chunks((ctx_limit + kAttnChunk - 1) / kAttnChunk, batch * nkv, passes, p.n_splits);
+  } else if (p.grouped && rows > 0) {
+    q.groups = short_groups(batch * nkv * p.n_splits, passes);
   }
   q.splits = splits_with_keys(q.chunks, ctx_limit, rows, C);
   return q;

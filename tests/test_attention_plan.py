@@ -1,7 +1,7 @@
 """The attention's plan on the host: csrc/lsv_attn_plan.h is plain C++, built here with the host
 compiler and compared over batches, head counts, row bounds and contexts.
 
-* a block of up to 64 rows has the same splits under every row bound, in one query group;
+* a block of up to 64 rows has the same splits under every row bound;
 * the splits of a sequence cover its keys and never exceed the partial buffers';
 * the packed grid has a workgroup for every (sequence, query group, kv head, split) of any rows
   under the bound."""
@@ -23,7 +23,7 @@ extern "C" void plan(int batch, int nkv, int group, int max_rows, int max_ctx, i
 extern "C" void sequence(int batch, int nkv, int group, int max_rows, int max_ctx, int rows, int C, int M, int* q) {
   const SeqPlan s = seq_plan(plan_attention(batch, nkv, group, max_rows, max_ctx), batch, nkv, max_ctx,
                              rows, C, M);
-  q[0] = s.splits, q[1] = s.chunks, q[2] = s.groups;
+  q[0] = s.splits, q[1] = s.chunks, q[2] = s.groups, q[3] = s.coarse;
 }
 """
 HEADS = [(8, 4), (8, 5), (8, 8), (2, 4), (2, 2), (1, 16), (8, 1)]
@@ -47,7 +47,7 @@ def plan(lib, *args):
 
 
 def sequence(lib, *args):
-    q = (ctypes.c_int * 3)()
+    q = (ctypes.c_int * 4)()
     lib.sequence(*args, q)
     return list(q)
 
@@ -62,8 +62,11 @@ def test_short_blocks_have_one_plan_under_every_row_bound(lib):
                     for rows in (1, 17, 64):
                         C = max(0, ctx - 70)
                         if rows <= bound:
-                            assert (sequence(lib, batch, nkv, group, bound, ctx, rows, C, 64) ==
-                                    [-(-min(-(-(C + rows) // 64), -(-ctx // 64)) // base[1]), base[1], 1])
+                            splits, chunks, groups, coarse = sequence(lib, batch, nkv, group, bound, ctx, rows, C, 64)
+                            assert splits == -(-min(-(-(C + rows) // 64), -(-ctx // 64)) // base[1])
+                            assert chunks == base[1] and not coarse
+                            assert groups == 1 or (groups <= -(-rows * group // 128) and
+                                                   batch * nkv * base[0] * groups <= 256)
 
 
 def test_grid_and_partials_hold_every_block_under_the_bound(lib):
@@ -88,10 +91,10 @@ def test_grid_and_partials_hold_every_block_under_the_bound(lib):
                         units = 0
                         for b in range(batch):
                             C = ctx - rows[b] if kind != 4 else rng.randint(0, ctx - rows[b])
-                            s, chunks, groups = sequence(lib, batch, nkv, group, bound, ctx, rows[b], C, sum(rows))
+                            s, chunks, groups, coarse = sequence(lib, batch, nkv, group, bound, ctx, rows[b], C, sum(rows))
                             assert s <= n_splits and (rows[b] == 0 or s * chunks * 64 >= C + rows[b])
                             assert rows[b] == 0 or (s - 1) * chunks * 64 < C + rows[b]
-                            assert groups == 1 or groups * 8 * 16 >= rows[b] * group
+                            assert not coarse or groups * 8 * 16 >= rows[b] * group
                             units += s * groups * nkv
                         if packed:
                             assert units <= n_wgs, (nkv, group, batch, ctx, bound, rows)
@@ -111,8 +114,8 @@ def test_query_groups_walk_hardly_longer_than_passes_would(lib):
                     if rows > ctx:
                         continue
                     n_splits, per_split = plan(lib, batch, nkv, group, bound, ctx)[:2]
-                    s, chunks, groups = sequence(lib, batch, nkv, group, bound, ctx, rows, ctx - rows, rows * batch)
-                    if groups == 1:
+                    s, chunks, groups, coarse = sequence(lib, batch, nkv, group, bound, ctx, rows, ctx - rows, rows * batch)
+                    if not coarse:
                         continue
                     passes = -(-rows * group // 128)
                     walk = -(-batch * nkv * groups * s // 256) * chunks
